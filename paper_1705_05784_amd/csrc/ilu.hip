@@ -18,6 +18,7 @@
 
 #include "band.hpp"
 #include "internal.hpp"
+#include "ready.hpp"
 
 namespace fams {
 namespace {
@@ -173,85 +174,28 @@ __global__ void k_ilu_rows(const int* rows, int r0, int r1, const int* rp, const
 // 64/32-bit stores and loads, so no separate flag or fence is needed).  A wait
 // is bounded: past the spin limit the kernel flags an error and moves on, so
 // every wave always exits.
-template <class T> struct Sentinel;
-template <> struct Sentinel<double> {
-  using U = unsigned long long;
-  static constexpr U bits = 0x7FF4000000000BADull;
-};
-template <> struct Sentinel<float> {
-  using U = unsigned int;
-  static constexpr U bits = 0x7FA00BADu;
-};
 
-template <class T>
-__device__ __forceinline__ void store_ready(T* p, T v) {
-  using U = typename Sentinel<T>::U;
-  U u;
-  __builtin_memcpy(&u, &v, sizeof(T));
-  if (u == Sentinel<T>::bits) u ^= 1;  // never publish the sentinel itself
-  __hip_atomic_store(reinterpret_cast<U*>(p), u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-template <class T>
-__device__ __forceinline__ typename Sentinel<T>::U load_raw(const T* p) {
-  using U = typename Sentinel<T>::U;
-  return __hip_atomic_load(reinterpret_cast<const U*>(p), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Wait until *p is published, given a first read u of it.  Polls back off up
-// to ~0.4 us; the wait gives up after `limit` wall-clock ticks, or at once
-// when another wait has given up (err != 0), so a broken dependency order
-// ends the kernel quickly.  A wait that ends after more than limit / 2048
-// ticks (about 1 ms) is counted in err[1]: waits that long mean the
-// workgroups holding the dependencies were not running (another process's
-// work on the device), the first sign before a wait runs out.
-template <class T>
-__device__ __forceinline__ T wait_ready(const T* p, typename Sentinel<T>::U u, int* err,
-                                        unsigned long long limit) {
-  using U = typename Sentinel<T>::U;
-  const U* q = reinterpret_cast<const U*>(p);
-  if (u == Sentinel<T>::bits) {
-    const unsigned long long t0 = wall_clock64();
-    int backoff = 1;
-    while (u == Sentinel<T>::bits) {
-      for (int k = 0; k < backoff; ++k) __builtin_amdgcn_s_sleep(1);
-      backoff = backoff < 16 ? 2 * backoff : 16;
-      u = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (u != Sentinel<T>::bits) {
-        if (wall_clock64() - t0 > (limit >> 11)) atomicAdd(err + 1, 1);
-        break;
-      }
-      if (wall_clock64() - t0 > limit ||
-          __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-        atomicOr(err, 2);
-        u = 0;
-        break;
-      }
-    }
-  }
-  T v;
-  __builtin_memcpy(&v, &u, sizeof(T));
-  return v;
-}
-
-// s -= sum_{p in [p0, p1)} lu[p] x[ci[p]], waiting for each x entry.  The
-// reads of up to kDeps dependencies are issued together, so a row that finds
-// them published pays one memory round trip, not one per dependency.
+// s -= lu[p] x[ci[p]] for p = p0, p0 + kStep, ... (m terms), waiting for each
+// x entry.  The reads of up to kDeps dependencies are issued together, so a
+// row that finds them published pays one memory round trip, not one per
+// dependency.
 constexpr int kDeps = 8;
 
-template <class T>
-__device__ __forceinline__ void dot_ready(T& s, int p0, int p1, const int* ci, const T* lu,
+template <class T, int kStep>
+__device__ __forceinline__ void dot_ready(T& s, int p0, int m, const int* ci, const T* lu,
                                           const T* x, int* err, unsigned long long limit) {
   using U = typename Sentinel<T>::U;
-  for (int pb = p0; pb < p1; pb += kDeps) {
+  for (int k0 = 0; k0 < m; k0 += kDeps) {
     U u[kDeps];
 #pragma unroll
     for (int k = 0; k < kDeps; ++k)
-      if (pb + k < p1) u[k] = load_raw<T>(x + ci[pb + k]);
+      if (k0 + k < m) u[k] = load_raw<T>(x + ci[p0 + kStep * (k0 + k)]);
 #pragma unroll
     for (int k = 0; k < kDeps; ++k)
-      if (pb + k < p1) s -= lu[pb + k] * wait_ready<T>(x + ci[pb + k], u[k], err, limit);
+      if (k0 + k < m) {
+        const int p = p0 + kStep * (k0 + k);
+        s = fmadd(-lu[p], wait_ready<T>(x + ci[p], u[k], err, limit), s);
+      }
   }
 }
 
@@ -260,6 +204,12 @@ __global__ void k_fill_sentinel(int n, T* x) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   using U = typename Sentinel<T>::U;
   if (i < n) reinterpret_cast<U*>(x)[i] = Sentinel<T>::bits;
+}
+
+template <class T>
+__global__ void k_two_stage_sum(int n, const T* a, const T* x, double* y) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) y[i] = static_cast<double>(a[i]) + static_cast<double>(x[i]);
 }
 
 // forward sweep y = L^{-1} b (unit L); also arms z (the backward sweep's
@@ -280,7 +230,7 @@ k_sweep_lower(const int* rows, const int* chunk, int nchunks, const int* rp, con
     if (t < chunk[c + 1]) {
       const int i = rows[t];
       T s = b[i];
-      dot_ready<T>(s, rp[i], diag[i], ci, lu, y, err, limit);
+      dot_ready<T, 1>(s, rp[i], diag[i] - rp[i], ci, lu, y, err, limit);
       using U = typename Sentinel<T>::U;
       reinterpret_cast<U*>(z)[i] = Sentinel<T>::bits;
       store_ready<T>(y + i, s);
@@ -305,158 +255,9 @@ k_sweep_upper(const int* rows, const int* chunk, int nchunks, const int* rp, con
     if (t < chunk[c + 1]) {
       const int i = rows[t];
       T s = y[i];
-      dot_ready<T>(s, diag[i] + 1, rp[i + 1], ci, lu, z, err, limit);
+      // descending columns, the order in which the dependencies finish
+      dot_ready<T, -1>(s, rp[i + 1] - 1, rp[i + 1] - 1 - diag[i], ci, lu, z, err, limit);
       store_ready<T>(z + i, s / lu[diag[i]]);
-    }
-  }
-}
-
-// Range sweeps.  A workgroup takes ranges in ticket order (ascending for the
-// forward sweep, descending for the backward one) and walks a range level by
-// level with a barrier between levels; values of rows inside the range are
-// read from LDS, values of rows in earlier ranges are waited for in global
-// memory, and every row is published there (value as ready flag) for the
-// ranges after it.  While a level is computed, each thread already loads
-// its row of the next level (ELL dependencies, factor values, and the first
-// read of its dependencies outside the range), so the barrier, LDS reads
-// and arithmetic are all that a level costs on the critical path.  A range
-// depends only on earlier tickets, whose workgroups are already running, so
-// the schedule always progresses; every wait is bounded as above.
-template <class T>
-struct SweepRow {
-  using U = typename Sentinel<T>::U;
-  int t, i, cnt;
-  T in, dg;
-  int col[kEll];
-  T val[kEll];
-  U raw[kEll];
-};
-
-// the part of a row's data addressed by its sweep position t alone (the
-// input is gathered into sweep order beforehand)
-// (loads are issued unconditionally -- position 0 stands in for "no row" --
-// so every thread issues the same number of loads per level and the
-// compiler's wait counts stay exact instead of draining all loads in flight)
-template <class T>
-__device__ __forceinline__ void fetch_static(SweepRow<T>& w, int t, const int* rows,
-                                             const int* ecol, const T* eval, const int* ecnt,
-                                             const T* ediag, const T* inp) {
-  w.t = t;
-  const int64_t u = t < 0 ? 0 : t;
-  w.i = rows[u];
-  w.cnt = ecnt[u];
-  w.dg = ediag[u];
-  w.in = inp[u];
-#pragma unroll
-  for (int k = 0; k < kEll; ++k) {
-    w.col[k] = ecol[u * kEll + k];
-    w.val[k] = eval[u * kEll + k];
-  }
-}
-
-// first read of every dependency in global memory (only those outside the
-// range [lo, hi) are used later; the others come from LDS)
-template <class T>
-__device__ __forceinline__ void fetch_raw(SweepRow<T>& w, const T* g) {
-#pragma unroll
-  for (int k = 0; k < kEll; ++k) w.raw[k] = load_raw<T>(g + max(w.col[k], 0));
-}
-
-template <class T, bool kUpper>
-__device__ __forceinline__ void sweep_row(const SweepRow<T>& w, int lo, int hi, T* loc, T* g,
-                                          T* arm, const int* ep0, const int* ci, const T* lu,
-                                          int* err, unsigned long long limit) {
-  using U = typename Sentinel<T>::U;
-  T s = w.in;
-#pragma unroll
-  for (int k = 0; k < kEll; ++k) {
-    const int j = w.col[k];
-    if (j >= 0) {
-      T v;
-      if (j >= lo && j < hi) v = loc[j - lo];
-      else v = wait_ready<T>(g + j, w.raw[k], err, limit);
-      s -= w.val[k] * v;
-    }
-  }
-  if (w.cnt > kEll) {  // dependencies past the ELL width, from the CSR
-    const int p0 = ep0[w.t];
-    for (int p = p0 + kEll; p < p0 + w.cnt; ++p) {
-      const int j = ci[p];
-      T v;
-      if (j >= lo && j < hi) v = loc[j - lo];
-      else v = wait_ready<T>(g + j, load_raw<T>(g + j), err, limit);
-      s -= lu[p] * v;
-    }
-  }
-  if constexpr (kUpper) s = s / w.dg;
-  else reinterpret_cast<U*>(arm)[w.i] = Sentinel<T>::bits;
-  loc[w.i - lo] = s;
-  store_ready<T>(g + w.i, s);
-}
-
-// Range sweep kernel.  Each thread keeps four levels in flight in a register
-// ring: at level k it issues the position-addressed loads of level k+3 and
-// the outside-range reads of level k+2, then computes its row of level k
-// (loads are issued ~3 levels before use, so a level costs about a barrier
-// and its arithmetic).  The level loop is unrolled by four so the ring is
-// indexed at compile time.
-template <class T, bool kUpper>
-__global__ void __launch_bounds__(256)
-k_sweep_ranges(int n, int S, int nranges, const int* rows, const int* seg, const int* segbase,
-               const int* ecol, const T* eval, const int* ecnt, const int* ep0, const T* ediag,
-               const int* ci, const T* lu, const T* inp, T* out, T* arm, int* ticket, int* err,
-               unsigned long long limit) {
-  // dynamic LDS: the range's values (S entries of T), then its level
-  // boundaries (max_segs + 1 ints; always in LDS, so every read of them is
-  // an LDS read and never waits on the global loads in flight)
-  extern __shared__ double lds_raw[];
-  T* loc = reinterpret_cast<T*>(lds_raw);
-  int* s_seg = reinterpret_cast<int*>(loc + S);
-  __shared__ int s_c;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  while (true) {
-    if (tid == 0) s_c = atomicAdd(ticket, 1);
-    __syncthreads();
-    const int c = s_c;
-    if (c >= nranges) break;
-    const int r = kUpper ? nranges - 1 - c : c;
-    const int r0 = r * S, r1 = min(n, r0 + S);
-    const int sb = segbase[r], ns = segbase[r + 1] - sb;
-    for (int k = tid; k <= ns; k += nt) s_seg[k] = seg[sb + k];
-    __syncthreads();
-    auto segat = [&](int k) { return s_seg[k]; };
-    auto pos = [&](int lvl) {
-      if (lvl >= ns) return -1;
-      const int t = segat(lvl) + tid;
-      return t < segat(lvl + 1) ? t : -1;
-    };
-    auto fst = [&](SweepRow<T>& w, int lvl) {
-      fetch_static<T>(w, pos(lvl), rows, ecol, eval, ecnt, ediag, inp);
-    };
-    auto step = [&](int lvl, SweepRow<T>& cur, SweepRow<T>& n2, SweepRow<T>& n3) {
-      fst(n3, lvl + 3);
-      fetch_raw<T>(n2, out);
-      if (cur.t >= 0) sweep_row<T, kUpper>(cur, r0, r1, loc, out, arm, ep0, ci, lu, err, limit);
-      const int a = segat(lvl), b = segat(lvl + 1);
-      for (int t = a + tid + nt; t < b; t += nt) {  // levels wider than the workgroup
-        SweepRow<T> w;
-        fetch_static<T>(w, t, rows, ecol, eval, ecnt, ediag, inp);
-        fetch_raw<T>(w, out);
-        sweep_row<T, kUpper>(w, r0, r1, loc, out, arm, ep0, ci, lu, err, limit);
-      }
-      lds_barrier();  // the level's values in loc; global traffic stays in flight
-    };
-    SweepRow<T> s0, s1, s2, s3;
-    fst(s0, 0);
-    fst(s1, 1);
-    fst(s2, 2);
-    fetch_raw<T>(s0, out);
-    fetch_raw<T>(s1, out);
-    for (int k = 0; k < ns; k += 4) {
-      step(k, s0, s2, s3);
-      if (k + 1 < ns) step(k + 1, s1, s3, s0);
-      if (k + 2 < ns) step(k + 2, s2, s0, s1);
-      if (k + 3 < ns) step(k + 3, s3, s1, s2);
     }
   }
 }
@@ -697,42 +498,6 @@ k_ilu_ranges(int n, int nranges, const int* seg, const int* segbase, IluRecs R, 
   }
 }
 
-// x[t] = v[rows[t]]: a sweep's input in sweep order
-template <class T>
-__global__ void k_gather(int n, const int* rows, const T* v, T* x) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) x[t] = v[rows[t]];
-}
-
-// ELL form of the dependencies of every position of a range schedule
-__global__ void k_ell_build(int n, int upper, const int* rows, const int* rp, const int* diag,
-                            const int* ci, int* ecol, int* epos, int* ecnt, int* ep0) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  const int i = rows[t];
-  const int p0 = upper ? diag[i] + 1 : rp[i];
-  const int p1 = upper ? rp[i + 1] : diag[i];
-  ecnt[t] = p1 - p0;
-  ep0[t] = p0;
-  for (int k = 0; k < kEll; ++k) {
-    const bool in = p0 + k < p1;
-    ecol[static_cast<int64_t>(t) * kEll + k] = in ? ci[p0 + k] : -1;
-    epos[static_cast<int64_t>(t) * kEll + k] = in ? p0 + k : -1;
-  }
-}
-
-template <class T>
-__global__ void k_ell_vals(int n, const int* rows, const int* diag, const int* epos,
-                           const T* lu, T* eval, T* ediag) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  for (int k = 0; k < kEll; ++k) {
-    const int p = epos[static_cast<int64_t>(t) * kEll + k];
-    eval[static_cast<int64_t>(t) * kEll + k] = p >= 0 ? lu[p] : T(0);
-  }
-  ediag[t] = lu[diag[rows[t]]];
-}
-
 }  // namespace
 
 // bound of one dataflow wait: 2 s of the device's constant-rate clock
@@ -826,7 +591,7 @@ int sweep_range_rows(Handle* h) {
 // a range, rows of equal level are independent and every dependency inside
 // the range has a lower level, so a workgroup can take the range level by
 // level with a barrier between levels (counting sort per range, host side)
-void range_table(Handle* h, const std::vector<int>& lev, int S, int upper, Ranges* R) {
+void range_table(Handle* h, const std::vector<int>& lev, int S, Ranges* R) {
   const int n = h->n;
   const int nr = (n + S - 1) / S;
   std::vector<int> rows(n), seg, segbase(nr + 1);
@@ -860,30 +625,7 @@ void range_table(Handle* h, const std::vector<int>& lev, int S, int upper, Range
                       h->stream));
   HIPX(hipMemcpyAsync(R->segbase, segbase.data(), (nr + 1) * sizeof(int), hipMemcpyHostToDevice,
                       h->stream));
-  const size_t ne = static_cast<size_t>(n) * kEll;
-  R->ecol.reset(&h->alloc, ne);
-  R->epos.reset(&h->alloc, ne);
-  R->ecnt.reset(&h->alloc, n);
-  R->ep0.reset(&h->alloc, n);
-  LAUNCH(h, "ilu_ell", k_ell_build, blocks_for(n, kT), kT, 0, n, upper, R->rows.get(),
-         h->rp.get(), h->diag.get(), h->ci.get(), R->ecol.get(), R->epos.get(), R->ecnt.get(),
-         R->ep0.get());
-  R->eval64.free();  // the ELL values follow the factors: taken again on the next sweep
-  R->ediag64.free();
-  R->eval32.free();
-  R->ediag32.free();
   HIPX(hipStreamSynchronize(h->stream));
-}
-
-// factor values of a range schedule in precision T (gathered once)
-template <class T>
-void ell_values(Handle* h, Ranges* R, const T* lu, DBuf<T>& ev, DBuf<T>& ed) {
-  if (ev.get()) return;
-  const int n = h->n;
-  ev.reset(&h->alloc, static_cast<size_t>(n) * kEll);
-  ed.reset(&h->alloc, n);
-  LAUNCH(h, "ilu_ell", k_ell_vals<T>, blocks_for(n, kT), kT, 0, n, R->rows.get(),
-         h->diag.get(), R->epos.get(), lu, ev.get(), ed.get());
 }
 
 // chunks of at most 256 rows inside one level
@@ -924,8 +666,7 @@ void build_ilu(Handle* h) {
   chunk_table(h, &h->lvl_lo);
   chunk_table(h, &h->lvl_up);
   if (const int S = sweep_range_rows(h)) {
-    range_table(h, lev_lo, S, 0, &h->rng_lo);
-    range_table(h, lev_up, S, 1, &h->rng_up);
+    range_table(h, lev_lo, S, &h->rng_lo);
   }
   pt.mark("ilu schedules");
   h->info.ilu_levels_lower = h->lvl_lo.count();
@@ -979,23 +720,19 @@ void build_ilu(Handle* h) {
            h->ilu32.get());
   }
   // everything the sweeps keep in the handle, allocated now so that applying
-  // the smoother allocates nothing: work tickets, the wait error word, the
-  // sweep-order input and the factor values in the schedules' ELL form
+  // the smoother allocates nothing
   if (!h->ilu_ticket.get()) h->ilu_ticket.reset(&h->alloc, kTicketInts);
   if (!h->sweep_err.get()) {
     h->sweep_err.reset(&h->alloc, 2);   // error bits, long waits
     HIPX(hipMemsetAsync(h->sweep_err, 0, 2 * sizeof(int), h->stream));
   }
-  if (h->rng_lo.nranges > 0) {
-    if (h->precision == FAMS_PREC_MIXED) {
-      if (!h->sweep_in32.get()) h->sweep_in32.reset(&h->alloc, n);
-      ell_values<float>(h, &h->rng_lo, h->ilu32.get(), h->rng_lo.eval32, h->rng_lo.ediag32);
-      ell_values<float>(h, &h->rng_up, h->ilu32.get(), h->rng_up.eval32, h->rng_up.ediag32);
-    } else {
-      if (!h->sweep_in64.get()) h->sweep_in64.reset(&h->alloc, n);
-      ell_values<double>(h, &h->rng_lo, h->ilu.get(), h->rng_lo.eval64, h->rng_lo.ediag64);
-      ell_values<double>(h, &h->rng_up, h->ilu.get(), h->rng_up.eval64, h->rng_up.ediag64);
+  if (const int cap = sweep_range_rows(h)) {
+    if (h->tiles.ph.empty()) build_tiles(h, cap);
+    if (!h->tiles.ph.empty()) {
+      if (h->precision == FAMS_PREC_MIXED) tile_values<float>(h, h->ilu32.get());
+      else tile_values<double>(h, h->ilu.get());
     }
+    pt.mark("ilu tiles");
   }
 }
 
@@ -1073,55 +810,15 @@ void build_block_smoother(Handle* h) {
 
 // x = U^{-1} L^{-1} b.  `y` is scratch of n entries.
 template <class T>
-void ilu_apply(Handle* h, const T* lu, const T* b, T* x, T* y) {
-  if (!h->ilu_ticket.get()) h->ilu_ticket.reset(&h->alloc, kTicketInts);
-  if (!h->sweep_err.get()) {
-    h->sweep_err.reset(&h->alloc, 2);   // error bits, long waits
-    HIPX(hipMemsetAsync(h->sweep_err, 0, 2 * sizeof(int), h->stream));
+void ilu_apply(Handle* h, const T* lu, const T* b, T* x, T* y, const T* add, double* sum) {
+  if (!h->tiles.ph.empty()) {
+    tile_apply<T>(h, lu, b, x, add, sum);
+    return;
   }
   HIPX(hipMemsetAsync(h->ilu_ticket, 0, 2 * sizeof(int), h->stream));
   const int n = h->n;
   LAUNCH(h, "ilu_arm", k_fill_sentinel<T>, blocks_for(n, kT), kT, 0, n, y);
   wait_limit(h);
-  if (h->rng_lo.nranges > 0) {
-    Ranges& L = h->rng_lo;
-    Ranges& U = h->rng_up;
-    const T *lv, *ld, *uv, *ud;
-    if constexpr (std::is_same<T, double>::value) {
-      ell_values<double>(h, &L, lu, L.eval64, L.ediag64);
-      ell_values<double>(h, &U, lu, U.eval64, U.ediag64);
-      lv = L.eval64.get(); ld = L.ediag64.get(); uv = U.eval64.get(); ud = U.ediag64.get();
-    } else {
-      ell_values<float>(h, &L, lu, L.eval32, L.ediag32);
-      ell_values<float>(h, &U, lu, U.eval32, U.ediag32);
-      lv = L.eval32.get(); ld = L.ediag32.get(); uv = U.eval32.get(); ud = U.ediag32.get();
-    }
-    const size_t lds = static_cast<size_t>(L.S) * sizeof(T) +
-                       static_cast<size_t>(std::max(L.max_segs, U.max_segs) + 1) * sizeof(int);
-    FAMS_REQUIRE(lds <= static_cast<size_t>(lds_hw_budget(h)), FAMS_ERR_CAPACITY,
-                 "ILU range schedule does not fit in LDS");
-    allow_lds(reinterpret_cast<const void*>(&k_sweep_ranges<T, false>), lds);
-    allow_lds(reinterpret_cast<const void*>(&k_sweep_ranges<T, true>), lds);
-    T* inp;
-    if constexpr (std::is_same<T, double>::value) {
-      if (!h->sweep_in64.get()) h->sweep_in64.reset(&h->alloc, n);
-      inp = h->sweep_in64.get();
-    } else {
-      if (!h->sweep_in32.get()) h->sweep_in32.reset(&h->alloc, n);
-      inp = h->sweep_in32.get();
-    }
-    LAUNCH(h, "ilu_gather", k_gather<T>, blocks_for(n, kT), kT, 0, n, L.rows.get(), b, inp);
-    LAUNCH(h, "ilu_lower", (k_sweep_ranges<T, false>), std::min(L.nranges, 2048), 256, lds, n,
-           L.S, L.nranges, L.rows.get(), L.seg.get(), L.segbase.get(), L.ecol.get(), lv,
-           L.ecnt.get(), L.ep0.get(), ld, h->ci.get(), lu, inp, y, x, h->ilu_ticket.get(),
-           h->sweep_err.get(), h->wait_ticks);
-    LAUNCH(h, "ilu_gather", k_gather<T>, blocks_for(n, kT), kT, 0, n, U.rows.get(), y, inp);
-    LAUNCH(h, "ilu_upper", (k_sweep_ranges<T, true>), std::min(U.nranges, 2048), 256, lds, n,
-           U.S, U.nranges, U.rows.get(), U.seg.get(), U.segbase.get(), U.ecol.get(), uv,
-           U.ecnt.get(), U.ep0.get(), ud, h->ci.get(), lu, inp, x, nullptr,
-           h->ilu_ticket.get() + 1, h->sweep_err.get(), h->wait_ticks);
-    return;
-  }
   // a window of ~kSweepGroups chunks in flight: enough to overlap tens of
   // levels, few enough that waiting rows do not flood the memory system
   const int g_lo = std::min(h->lvl_lo.nchunks, kSweepGroups);
@@ -1132,6 +829,7 @@ void ilu_apply(Handle* h, const T* lu, const T* b, T* x, T* y) {
   LAUNCH(h, "ilu_upper", k_sweep_upper<T>, g_up, 256, 0, h->lvl_up.rows.get(),
          h->lvl_up.chunk.get(), h->lvl_up.nchunks, h->rp.get(), h->ci.get(), h->diag.get(), lu,
          y, x, h->ilu_ticket.get() + 1, h->sweep_err.get(), h->wait_ticks);
+  if (sum) LAUNCH(h, "add", k_two_stage_sum<T>, blocks_for(n, kT), kT, 0, n, add, x, sum);
 }
 
 namespace {
@@ -1290,7 +988,9 @@ FAMS_ILU_BLOCK(float, 16)
 FAMS_ILU_BLOCK(float, 32)
 #undef FAMS_ILU_BLOCK
 
-template void ilu_apply<double>(Handle*, const double*, const double*, double*, double*);
-template void ilu_apply<float>(Handle*, const float*, const float*, float*, float*);
+template void ilu_apply<double>(Handle*, const double*, const double*, double*, double*,
+                                const double*, double*);
+template void ilu_apply<float>(Handle*, const float*, const float*, float*, float*, const float*,
+                               double*);
 
 }  // namespace fams

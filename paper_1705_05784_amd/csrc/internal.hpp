@@ -217,22 +217,51 @@ struct Levels {
   int count() const { return ptr.empty() ? 0 : static_cast<int>(ptr.size()) - 1; }
 };
 
-// Schedule of one triangular sweep by row ranges: rows [r*S, (r+1)*S) form
+// Schedule of the factorisation by row ranges: rows [r*S, (r+1)*S) form
 // range r; `rows` lists each range's rows grouped by dependency level
 // (ascending level, then row); segment s = rows[seg[s] .. seg[s+1]) is one
 // level of one range, and range r owns segments [segbase[r], segbase[r+1]).
-// For the sweep kernels every position t of `rows` also carries its row's
-// dependencies in sweep order: the first kEll in ELL form (ecol[t*kEll+k],
-// -1 past the end, with the factor entry's CSR position epos), the count
-// ecnt[t] and the first CSR position ep0[t] for the rest; the factor values
-// are gathered per precision (evalN, ediagN) when the factors are known.
-constexpr int kEll = 8;
 struct Ranges {
   int S = 0, nranges = 0, max_segs = 0;
   DBuf<int> rows, seg, segbase;
-  DBuf<int> ecol, epos, ecnt, ep0;
-  DBuf<double> eval64, ediag64;
-  DBuf<float> eval32, ediag32;
+};
+
+// Tile schedule of the one-right-hand-side sweeps (tiles.hip).  Positions:
+// rows sorted by tile, then level; a phase holds rows [row0, row1) at the
+// positions of the same range, C dependency codes a position (at W places,
+// from code0 on).
+struct TilePhase {
+  int row0 = 0, row1 = 0, tile0 = 0, ntiles = 0;
+  bool boxes = false;                         // boxes of a grid, or runs of rows
+  int C = 0, W = 0, cap = 0, max_slices = 0;  // cap: most rows of a tile
+  size_t code0 = 0;
+};
+
+struct Bytes : DBuf<char> {
+  template <class T> T* as() const { return reinterpret_cast<T*>(get()); }
+};
+
+// factors and vectors in the schedule's order (FP64, or FP32 in the precision
+// form): the dependencies' values, the diagonal of U, the vector the sweeps
+// work on and the values that other tiles read (lower, upper)
+struct TileState {
+  Bytes lval, uval, udiag, x, hl, hu;
+};
+
+struct TileSched {
+  std::vector<TilePhase> ph;  // empty: no schedule
+  DBuf<int> pos, row, meta;   // row -> position, its inverse, flags per position
+  DBuf<int> tslice, slice;    // tile -> slices, slice -> first position
+  DBuf<int> lcol, ucol;
+  DBuf<int> pre;              // first-phase rows coupled to the second
+  int npre = 0;
+  DBuf<int> ticket;
+  TileState st;
+  bool armed = false;         // published values and tickets are in their initial state
+  void clear() {
+    ph.clear();
+    npre = 0;
+  }
 };
 
 // Host phase timer: with FAMS_SETUP_TIMING set, mark() synchronises the
@@ -292,9 +321,8 @@ struct Handle {
   DBuf<double> ilu;
   DBuf<float> ilu32;
   Levels lvl_lo, lvl_up;
-  Ranges rng_lo, rng_up;
-  DBuf<double> sweep_in64;  // a sweep's input gathered into sweep order
-  DBuf<float> sweep_in32;
+  Ranges rng_lo;  // the factorisation's schedule
+  TileSched tiles;
   DBuf<int> ilu_ticket;  // work tickets of the two sweeps
   DBuf<int> sweep_err;   // set when a bounded wait in a sweep gives up
   unsigned long long wait_ticks = 0;  // bound of one wait, device wall-clock ticks
@@ -402,12 +430,22 @@ unsigned long long wait_limit(Handle* h);
 void dense_gemm_add(Handle* h, int m, int p, int k, double alpha, const double* A, int lda,
                     const double* B, int ldb, double* C, int ldc);
 void coarse_apply(Handle* h, const double* inv, int nc, const double* x, double* y, double* part);
+// tiles.hip: schedule of the sweeps by tiles of at most `cap` rows, the
+// factors in its order, and x = U^{-1} L^{-1} b
+void build_tiles(Handle* h, int cap);
+template <class T>
+void tile_values(Handle* h, const T* lu);
+template <class T>
+void tile_apply(Handle* h, const T* lu, const T* b, T* x, const T* add, double* sum);
 // ilu.hip
 void build_ilu(Handle* h);
 // the per-medium smoothing stage's handle (smoother 2)
 void build_block_smoother(Handle* h);
+// x = U^{-1} L^{-1} b, or with `sum` only sum = add + x in FP64; with tiles, b
+// may be null (already in the schedule's order in tiles.st.x)
 template <class T>
-void ilu_apply(Handle* h, const T* lu, const T* b, T* x, T* y);
+void ilu_apply(Handle* h, const T* lu, const T* b, T* x, T* y, const T* add = nullptr,
+               double* sum = nullptr);
 // the same for K right-hand sides in lock-step, vectors interleaved x[i * K + r]
 template <class T, int K>
 void ilu_apply_block(Handle* h, const T* lu, const T* b, T* x, T* y,

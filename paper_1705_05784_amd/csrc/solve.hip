@@ -27,13 +27,15 @@ namespace {
 constexpr int kT = 256;
 constexpr int kRedBlocks = 512;
 
-// y = b - A x (b may be null: y = -A x); 8 lanes per row, so a wavefront
+// y = b - A x (b may be null: y = -A x; pos: row i's result goes to
+// y[pos[i]], the order of the ILU(0) sweeps); 8 lanes per row, so a wavefront
 // reads 8 consecutive rows' entries as one contiguous stretch; fixed-order
 // shuffle reduction (deterministic).
 constexpr int kSub = 8;
 template <class TV, class TX, class TB, class TY>
 __global__ void __launch_bounds__(256)
-k_resid(int n, const int* rp, const int* ci, const TV* val, const TX* x, const TB* b, TY* y) {
+k_resid(int n, const int* rp, const int* ci, const TV* val, const TX* x, const TB* b, TY* y,
+        const int* pos) {
   const int i = blockIdx.x * (blockDim.x / kSub) + threadIdx.x / kSub;
   const int l = threadIdx.x % kSub;
   double s = 0.0;
@@ -41,7 +43,8 @@ k_resid(int n, const int* rp, const int* ci, const TV* val, const TX* x, const T
     for (int p = rp[i] + l; p < rp[i + 1]; p += kSub)
       s += static_cast<double>(val[p]) * static_cast<double>(x[ci[p]]);
   for (int o = kSub / 2; o > 0; o >>= 1) s += __shfl_down(s, o, kSub);
-  if (i < n && l == 0) y[i] = static_cast<TY>((b ? static_cast<double>(b[i]) : 0.0) - s);
+  if (i < n && l == 0)
+    y[pos ? pos[i] : i] = static_cast<TY>((b ? static_cast<double>(b[i]) : 0.0) - s);
 }
 
 // y = M x with 8 lanes per row (see k_resid)
@@ -288,9 +291,9 @@ double norm_host(Handle* h, const double* a, int64_t n, double* part, double* sc
 }
 
 template <class TV, class TX, class TB, class TY>
-void resid(Handle* h, const TV* val, const TX* x, const TB* b, TY* y) {
+void resid(Handle* h, const TV* val, const TX* x, const TB* b, TY* y, const int* pos = nullptr) {
   LAUNCH(h, "spmv_resid", (k_resid<TV, TX, TB, TY>), blocks_for(h->n, kT / kSub), kT, 0, h->n,
-         h->rp.get(), h->ci.get(), val, x, b, y);
+         h->rp.get(), h->ci.get(), val, x, b, y, pos);
 }
 
 // Table 1 steps 5-7 on a residual r (FP64 in, FP64 out); T = stage type
@@ -331,10 +334,18 @@ void stage(Handle* h, const Work& k, const double* r, double* z) {
   coarse_apply(h, h->Ainv.get(), nc, k.rc, k.xc, k.gpart);
   LAUNCH(h, "prolong", (k_spmv8<T, double, T>), blocks_for(n, kT / kSub), kT, 0, n,
          h->p_rp.get(), h->p_ci.get(), pv, k.xc, d1);
-  if (h->smoother) {
+  if (h->smoother && !h->blk) {  // z = d1 + x is written by the upper sweep
+    if (!h->tiles.ph.empty()) {
+      resid<T, T, T, T>(h, av, d1, rT, h->tiles.st.x.as<T>(), h->tiles.pos.get());
+      ilu_apply<T>(h, lu, nullptr, nullptr, ysc, d1, z);
+    } else {
+      resid<T, T, T, T>(h, av, d1, rT, rh);
+      ilu_apply<T>(h, lu, rh, x, ysc, d1, z);
+    }
+  } else if (h->smoother) {
     resid<T, T, T, T>(h, av, d1, rT, rh);
     ilu_apply<T>(h, lu, rh, x, ysc);
-    if (h->blk) {  // per-medium stage: r <- r - A x (row by row, in place), x += M_B^{-1} r
+    {  // per-medium stage: r <- r - A x (row by row, in place), x += M_B^{-1} r
       Handle* b = h->blk.get();
       T* xb;
       const T* blu;
@@ -464,6 +475,7 @@ void check_sweeps(Handle* h) {
   HIPX(hipStreamSynchronize(h->stream));
   h->info.long_waits += e[1];
   HIPX(hipMemsetAsync(h->sweep_err.get() + 1, 0, sizeof(int), h->stream));
+  if (e[0] != 0) h->tiles.armed = false;
   FAMS_REQUIRE(e[0] == 0, FAMS_ERR_DEVICE, "ILU(0) sweep: a dependency wait exceeded its bound");
 }
 
