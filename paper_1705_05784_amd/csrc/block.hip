@@ -1211,6 +1211,18 @@ void free_block_workspace(Handle* h) {
   h->bpart.free();
   h->bred.free();
   h->bsmall.free();
+  for (Handle* g : {h, h->blk.get()})
+    if (g) {
+      g->btiles.K = 0;
+      g->btiles.hl.free();
+      g->btiles.hu.free();
+    }
+}
+
+void prepare_sweeps(Handle* h, int K) {
+  if (!h->smoother) return;
+  for (Handle* g : {h, h->blk.get()})
+    if (g) block_tiles_prepare(g, K);
 }
 
 // all or nothing: a failed allocation leaves no work space (bK = 0)
@@ -1220,9 +1232,13 @@ void ensure_block_workspace(Handle* h, int K, int m) {
     h->tiling_known = true;
     h->info.tiled_rows = h->tiling.sy ? h->tiling.nm : 0;
   }
-  if (h->bK == K && h->bm >= m && h->bwk.get()) return;
+  if (h->bK == K && h->bm >= m && h->bwk.get()) {
+    prepare_sweeps(h, K);  // the factors may be new
+    return;
+  }
   free_block_workspace(h);
   try {
+    prepare_sweeps(h, K);
     const size_t nk = static_cast<size_t>(h->n) * K;
     h->bwk.reset(&h->alloc, block_vectors(m) * nk);
     if (h->precision == FAMS_PREC_MIXED) h->bwk32.reset(&h->alloc, 6 * nk);
@@ -1604,6 +1620,7 @@ void solve_group(Handle* h, const double* q, double* p, int nr, const fams_solve
     HIPX(hipMemcpyAsync(eg, g->sweep_err.get(), sizeof(eg), hipMemcpyDeviceToHost, h->stream));
     HIPX(hipStreamSynchronize(h->stream));
     e |= eg[0];
+    if (eg[0]) g->btiles.armed = false;
     h->info.long_waits += eg[1];
   }
   FAMS_REQUIRE(e == 0, FAMS_ERR_DEVICE, "ILU(0) sweep: a dependency wait exceeded its bound");

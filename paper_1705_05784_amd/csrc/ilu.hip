@@ -732,6 +732,7 @@ void build_ilu(Handle* h) {
       if (h->precision == FAMS_PREC_MIXED) tile_values<float>(h, h->ilu32.get());
       else tile_values<double>(h, h->ilu.get());
     }
+    h->btiles.values = false;
     pt.mark("ilu tiles");
   }
 }
@@ -942,6 +943,10 @@ void block_chunk_table(Handle* h, Levels* L, int rows) {
 // y is scratch of n * K entries; with `sum`, also sum = add + x in FP64
 template <class T, int K>
 void ilu_apply_block(Handle* h, const T* lu, const T* b, T* x, T* y, const T* add, double* sum) {
+  if (h->btiles.K == K) {
+    block_tiles_apply<T, K>(h, lu, b, x, y, add, sum);
+    return;
+  }
   if (!h->ilu_ticket.get()) h->ilu_ticket.reset(&h->alloc, kTicketInts);
   if (!h->sweep_err.get()) {
     h->sweep_err.reset(&h->alloc, 2);   // error bits, long waits

@@ -233,6 +233,7 @@ struct Ranges {
 struct TilePhase {
   int row0 = 0, row1 = 0, tile0 = 0, ntiles = 0;
   bool boxes = false;                         // boxes of a grid, or runs of rows
+  bool over = false;                          // some rows have more dependencies
   int C = 0, W = 0, cap = 0, max_slices = 0;  // cap: most rows of a tile
   size_t code0 = 0;
 };
@@ -262,6 +263,16 @@ struct TileSched {
     ph.clear();
     npre = 0;
   }
+};
+
+// The schedule's part for lock-step sweeps (btiles.hip), built on first use:
+// slice and tile of every position, the slots of published rows (lower,
+// upper), the rows' records, and the published values of groups of K.
+struct BlockTiles {
+  DBuf<int> sno, tile_of, lo, up, ticket;
+  int nlo = 0, nup = 0, K = 0;  // K = 0: no values allocated
+  Bytes lrec, urec, hl, hu;
+  bool values = false, armed = false;
 };
 
 // Host phase timer: with FAMS_SETUP_TIMING set, mark() synchronises the
@@ -323,6 +334,7 @@ struct Handle {
   Levels lvl_lo, lvl_up;
   Ranges rng_lo;  // the factorisation's schedule
   TileSched tiles;
+  BlockTiles btiles;
   DBuf<int> ilu_ticket;  // work tickets of the two sweeps
   DBuf<int> sweep_err;   // set when a bounded wait in a sweep gives up
   unsigned long long wait_ticks = 0;  // bound of one wait, device wall-clock ticks
@@ -437,6 +449,10 @@ template <class T>
 void tile_values(Handle* h, const T* lu);
 template <class T>
 void tile_apply(Handle* h, const T* lu, const T* b, T* x, const T* add, double* sum);
+// btiles.hip: the same for K right-hand sides in lock-step
+bool block_tiles_prepare(Handle* h, int K);
+template <class T, int K>
+void block_tiles_apply(Handle* h, const T* lu, const T* b, T* x, T* y, const T* add, double* sum);
 // ilu.hip
 void build_ilu(Handle* h);
 // the per-medium smoothing stage's handle (smoother 2)

@@ -48,6 +48,7 @@
 namespace fams {
 namespace {
 
+constexpr int kTurnSpins = 1 << 24;
 constexpr int kT = 256;
 constexpr int kRunRows = 4096;     // rows of a tile of consecutive rows
 constexpr int kBoxX = 128;         // cells of a box along x
@@ -347,45 +348,6 @@ __global__ void k_pre_upper(int m, const int* list, int row1, const int* pos, co
   X[t] = s;
 }
 
-// Buffer accesses: an offset past the buffer's end reads zero or is dropped,
-// so a wavefront issues them without branches and waits count exactly the
-// accesses that they need.  kCoherent is the cache policy of the device-scope
-// atomics in ready.hpp (sc1).
-constexpr int kCoherent = 16;
-constexpr int kNowhere = INT_MIN;  // 2^31 as an unsigned offset
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int64_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, static_cast<int>(bytes),
-                                           0x00020000);
-}
-
-template <class U, int kPolicy>
-__device__ __forceinline__ U buffer_get(__amdgpu_buffer_rsrc_t r, int off) {
-  U v;
-  if constexpr (sizeof(U) == 8) {
-    const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kPolicy);
-    __builtin_memcpy(&v, &w, 8);
-  } else {
-    const unsigned w = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kPolicy);
-    __builtin_memcpy(&v, &w, 4);
-  }
-  return v;
-}
-
-template <class U, int kPolicy>
-__device__ __forceinline__ void buffer_put(__amdgpu_buffer_rsrc_t r, int off, U v) {
-  if constexpr (sizeof(U) == 8) {
-    u32x2 w;
-    __builtin_memcpy(&w, &v, 8);
-    __builtin_amdgcn_raw_buffer_store_b64(w, r, off, 0, kPolicy);
-  } else {
-    unsigned w;
-    __builtin_memcpy(&w, &v, 4);
-    __builtin_amdgcn_raw_buffer_store_b32(w, r, off, 0, kPolicy);
-  }
-}
-
 // a row in flight: its first C dependencies, held at W = 4 or 8 places
 template <class T, int C>
 struct Entry {
@@ -577,16 +539,19 @@ k_tile_sweep(TileArgs<T> a) {
       }
       // the turn: groups 0 .. j - 1 done.  LDS accesses of a wavefront are in
       // order, so dependencies read after a turn word of j are final.
-      while (__hip_atomic_load(&s_turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < j - 1)
-        __builtin_amdgcn_s_sleep(1);
+      wait_turn<true>(&s_turn, j - 1, a.err, a.limit);
       T lv[C], x[G];
-      for (;;) {
+      for (int spin = 1;; ++spin) {
         const int f = __hip_atomic_load(&s_turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int q = 0; q < C; ++q) lv[q] = loc[idx[0][q]];
         asm volatile("" ::: "memory");
         if (__builtin_amdgcn_readfirstlane(f) >= j) break;
+        if (spin == kTurnSpins) {  // a guard: that turn always comes
+          atomicOr(a.err, 2);
+          break;
+        }
       }
 #pragma unroll
       for (int g = 0; g < G; ++g) {
@@ -754,6 +719,7 @@ void build_tiles(Handle* h, int cap) {
     // beyond eight they come from the CSR, a memory round trip each
     p.C = hs[2 + k] <= 3 ? 3 : hs[2 + k] <= 4 ? 4 : 8;
     p.W = p.C <= 4 ? 4 : 8;
+    p.over = hs[2 + k] > p.C;
     p.code0 = codes;
     codes += static_cast<size_t>(p.row1 - p.row0) * p.W;
   }
