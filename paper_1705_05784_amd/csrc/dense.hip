@@ -720,7 +720,7 @@ constexpr int kGT = 64, kGK = 16;
 
 __global__ void __launch_bounds__(256)
 k_gemm_mfma(int m, int p, int k, double alpha, const double* A, int lda, const double* B,
-            int ldb, double* C, int ldc, int skip0, int skip1, int overwrite) {
+            int ldb, double* C, int ldc, int skip0, int skip1, int overwrite, int bt) {
   __shared__ double As[kGK][kGT + 1];
   __shared__ double Bs[kGK][kGT + 1];
   const int r0 = blockIdx.x * kGT, c0 = blockIdx.y * kGT;
@@ -735,8 +735,11 @@ k_gemm_mfma(int m, int p, int k, double alpha, const double* A, int lda, const d
     for (int e = tid; e < kGK * kGT; e += 256) {
       const int i = e % kGT, qa = e / kGT;
       As[qa][i] = (r0 + i < m && k0 + qa < k) ? A[static_cast<int64_t>(k0 + qa) * lda + r0 + i] : 0.0;
-      const int qb = e % kGK, j = e / kGK;
-      Bs[qb][j] = (c0 + j < p && k0 + qb < k) ? B[static_cast<int64_t>(c0 + j) * ldb + k0 + qb] : 0.0;
+      const int qb = bt ? qa : e % kGK, j = bt ? i : e / kGK;
+      Bs[qb][j] = (c0 + j < p && k0 + qb < k)
+                      ? B[bt ? static_cast<int64_t>(k0 + qb) * ldb + c0 + j
+                             : static_cast<int64_t>(c0 + j) * ldb + k0 + qb]
+                      : 0.0;
     }
     __syncthreads();
 #pragma unroll
@@ -785,7 +788,14 @@ k_gemm_mfma(int m, int p, int k, double alpha, const double* A, int lda, const d
 // tile, so the tiles an XCD runs at once share A's rows and B's columns in
 // its L2 (with the workgroups of a column of tiles spread over all XCDs,
 // every XCD streamed every operand tile from beyond its L2).
-constexpr int kBT = 128, kBK = 32, kBPad = kBT + 4, kGroupRows = 8;
+// kBt: B is given transposed (p x k, the layout of A), so both operands are
+// staged along their contiguous direction; LDS rows of 128 + 16 doubles put the
+// two rows that a read touches on different banks (staging a column-major B
+// transposed wants 128 + 4).  Slices of 16: two workgroups a CU.  The 36
+// products of an inverse of n = 17810 (5.9 TFLOP): slices of 32 with B column-
+// major 148 ms, transposed 145 ms, slices of 16 120 ms (53 TFLOP/s in the
+// large ones; a library product of this size reaches 71).
+constexpr int kBT = 128, kBK = 16, kGroupRows = 8;
 
 __device__ __forceinline__ void gemm_tile(int tr_n, int tc_n, int& tr, int& tc) {
   const int T = tr_n * tc_n, b = blockIdx.x;
@@ -825,11 +835,13 @@ __device__ __forceinline__ void gemm_tile_lower(int tn, int& tr, int& tc) {
 
 constexpr int kBThreads = 512, kBWc = 2;  // threads, column blocks per wavefront
 
+template <bool kBt>
 __global__ void __launch_bounds__(kBThreads)
 k_gemm_mfma128(int m, int p, int k, double alpha, const double* A, int lda, const double* B,
                int ldb, double* C, int ldc, int skip0, int skip1, int overwrite, int lower) {
-  __shared__ double As[2][kBK][kBPad];
-  __shared__ double Bs[2][kBK][kBPad];
+  constexpr int kPad = kBt ? kBT + 16 : kBT + 4;
+  __shared__ double As[2][kBK][kPad];
+  __shared__ double Bs[2][kBK][kPad];
   int tr, tc;
   if (lower) gemm_tile_lower((m + kBT - 1) / kBT, tr, tc);
   else gemm_tile((m + kBT - 1) / kBT, (p + kBT - 1) / kBT, tr, tc);
@@ -852,9 +864,10 @@ k_gemm_mfma128(int m, int p, int k, double alpha, const double* A, int lda, cons
       const bool oa = rr < m && kk < k;
       const double va = A[oa ? static_cast<int64_t>(kk) * lda + rr : 0];
       ra[u] = oa ? va : 0.0;
-      const int kb = k0 + bk, cc = c0 + bc + kCs * u;
+      const int kb = kBt ? k0 + ak + kAs * u : k0 + bk, cc = kBt ? c0 + ar : c0 + bc + kCs * u;
       const bool ob = cc < p && kb < k;
-      const double vb = B[ob ? static_cast<int64_t>(cc) * ldb + kb : 0];
+      const double vb = B[ob ? (kBt ? static_cast<int64_t>(kb) * ldb + cc
+                                    : static_cast<int64_t>(cc) * ldb + kb) : 0];
       rb[u] = ob ? vb : 0.0;
     }
   };
@@ -862,7 +875,8 @@ k_gemm_mfma128(int m, int p, int k, double alpha, const double* A, int lda, cons
 #pragma unroll
     for (int u = 0; u < kL; ++u) {
       As[buf][ak + kAs * u][ar] = ra[u];
-      Bs[buf][bk][bc + kCs * u] = rb[u];
+      if (kBt) Bs[buf][ak + kAs * u][ar] = rb[u];
+      else Bs[buf][bk][bc + kCs * u] = rb[u];
     }
   };
   v4d acc[4][kBWc];
@@ -917,12 +931,16 @@ void gemm_mfma(Handle* h, int m, int p, int k, double alpha, const double* A, in
   const int ow = overwrite ? 1 : 0;
   if (static_cast<int64_t>(blocks_for(m, kBT)) * blocks_for(p, kBT) >= 192) {
     const unsigned tm = blocks_for(m, kBT), tiles = lower ? tm * (tm + 1) / 2 : tm * blocks_for(p, kBT);
-    LAUNCH_ON(h, s, "gemm_mfma", k_gemm_mfma128, tiles, kBThreads, 0, m, p, k, alpha, A, lda, B,
-              ldb, C, ldc, skip0, skip1, ow, lower ? 1 : 0);
+    if (lower)
+      LAUNCH_ON(h, s, "gemm_mfma", k_gemm_mfma128<true>, tiles, kBThreads, 0, m, p, k, alpha, A, lda,
+                B, ldb, C, ldc, skip0, skip1, ow, 1);
+    else
+      LAUNCH_ON(h, s, "gemm_mfma", k_gemm_mfma128<false>, tiles, kBThreads, 0, m, p, k, alpha, A, lda,
+                B, ldb, C, ldc, skip0, skip1, ow, 0);
   } else {  // small products: more, smaller tiles keep the device busy
     dim3 grid(blocks_for(m, kGT), blocks_for(p, kGT));
     LAUNCH_ON(h, s, "gemm_mfma", k_gemm_mfma, grid, 256, 0, m, p, k, alpha, A, lda, B, ldb, C,
-              ldc, skip0, skip1, ow);
+              ldc, skip0, skip1, ow, lower ? 1 : 0);
   }
 }
 
@@ -1331,36 +1349,25 @@ __global__ void __launch_bounds__(256) k_sym_check(const double* a, int n, int* 
   if (bad) *flag = 1;
 }
 
-// Block k0's panel from the lower triangle, without its own rows (zero):
-// kRow = false: the column block C (n x nb, leading dimension n), kRow = true:
-// the row block B (nb x n, leading dimension nb).
+// Block k0's panel (n x nb) from the lower triangle, without its own rows
+// (zero): the column block C, or the row block B transposed (kRow).
 template <bool kRow>
 __global__ void __launch_bounds__(256)
 k_sym_panel(const double* a, int n, int k0, int nb, double* out) {
-  __shared__ double T[kPt][kPt + 1];  // [q][r]
+  __shared__ double T[kPt][kPt + 1];
   const int r0 = blockIdx.x * kPt, q0 = blockIdx.y * kPt;
   const int l = threadIdx.x % kPt, m = threadIdx.x / kPt;
-  for (int u = m; u < kPt; u += 8) {
-    if (r0 < k0) {  // stored as row k0 + q, column r
-      const int r = r0 + u, q = q0 + l;
-      if (q < nb) {
-        const double v = a[static_cast<int64_t>(r) * n + k0 + q];
-        T[l][u] = kRow ? v : -v;
-      }
-    } else {
-      const int r = r0 + l, q = q0 + u;
-      if (r < n && q < nb) T[u][l] = r < k0 + nb ? 0.0 : a[static_cast<int64_t>(k0 + q) * n + r];
-    }
+  if (r0 < k0) {  // stored as row k0 + q, column r
+    for (int u = m; u < kPt; u += 8)
+      if (q0 + l < nb) T[l][u] = a[static_cast<int64_t>(r0 + u) * n + k0 + q0 + l];
+    __syncthreads();
   }
-  __syncthreads();
   for (int u = m; u < kPt; u += 8) {
-    if constexpr (kRow) {
-      const int r = r0 + u, q = q0 + l;
-      if (r < n && q < nb) out[static_cast<int64_t>(r) * nb + q] = T[l][u];
-    } else {
-      const int r = r0 + l, q = q0 + u;
-      if (r < n && q < nb) out[static_cast<int64_t>(q) * n + r] = T[u][l];
-    }
+    const int r = r0 + l, q = q0 + u;
+    if (r >= n || q >= nb) continue;
+    out[static_cast<int64_t>(q) * n + r] = r0 < k0       ? (kRow ? T[u][l] : -T[u][l])
+                                           : r < k0 + nb ? 0.0
+                                                         : a[static_cast<int64_t>(k0 + q) * n + r];
   }
 }
 
@@ -1421,7 +1428,7 @@ k_sym_mirror(const double* a, int n, int k0, int nb, double* out, int ld) {
 //
 // A symmetric matrix (checked) takes n^3 flops of the 2 n^3: only the lower
 // triangle's tiles of E are formed, and B's new value is C's transposed.  On
-// n = 17810 the products take 148 ms where the full form takes 296.
+// n = 17810 the products take 120 ms.
 constexpr int kOb = 1024;
 
 bool spd_inverse(Handle* h, const double* a, double* inv, int n) {
@@ -1445,11 +1452,11 @@ bool spd_inverse(Handle* h, const double* a, double* inv, int n) {
       const unsigned tb = blocks_for(nb, kPt);
       LAUNCH(h, "gje_get", k_sym_mirror, dim3(tb, tb), 256, 0, inv, n, k0, nb, D.get(), nb);
       gje_inner(h, D, nb, info.get());
-      // C1 = -C D^{-1}, E += C1 B (R1 holds C, then B)
+      // C1 = -C D^{-1}, E += C1 B (R1 holds C, then B transposed)
       LAUNCH(h, "gje_get", k_sym_panel<false>, dim3(tn, tb), 256, 0, inv, n, k0, nb, R1.get());
       gemm_mfma(h, n, nb, nb, -1.0, R1, n, D, nb, C1, n, 0, 0, nullptr, true);
       LAUNCH(h, "gje_get", k_sym_panel<true>, dim3(tn, tb), 256, 0, inv, n, k0, nb, R1.get());
-      gemm_mfma(h, n, n, nb, 1.0, C1, n, R1, nb, inv, n, k0, k0 + nb, nullptr, false, true);
+      gemm_mfma(h, n, n, nb, 1.0, C1, n, R1, n, inv, n, k0, k0 + nb, nullptr, false, true);
       LAUNCH(h, "gje_put", k_sym_put, dim3(tn, tb), 256, 0, inv, n, k0, nb, C1.get(), D.get());
     }
     if (!asym) LAUNCH(h, "gje_put", k_sym_mirror, dim3(tn, tn), 256, 0, inv, n, 0, n, inv, n);
