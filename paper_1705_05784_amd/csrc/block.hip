@@ -1222,7 +1222,7 @@ void free_block_workspace(Handle* h) {
 void prepare_sweeps(Handle* h, int K) {
   if (!h->smoother) return;
   for (Handle* g : {h, h->blk.get()})
-    if (g) block_tiles_prepare(g, K);
+    if (g && !block_tiles_prepare(g, K)) ensure_levels(g);
 }
 
 // all or nothing: a failed allocation leaves no work space (bK = 0)

@@ -643,6 +643,22 @@ void chunk_table(Handle* h, Levels* L) {
 
 }  // namespace
 
+// level order of both triangles, where no tiles serve: the level-chunk sweeps
+// and the factorisation by ranges (or by levels)
+void ensure_levels(Handle* h) {
+  if (h->lvl_lo.count()) return;
+  std::vector<int> lev_lo, lev_up;
+  Levels* outs[2] = {&h->lvl_lo, &h->lvl_up};
+  std::vector<int>* hls[2] = {&lev_lo, &lev_up};
+  levels_both(h, outs, hls);
+  chunk_table(h, &h->lvl_lo);
+  chunk_table(h, &h->lvl_up);
+  if (const int S = sweep_range_rows(h))
+    if (h->tiles.ph.empty()) range_table(h, lev_lo, S, &h->rng_lo);
+  h->info.ilu_levels_lower = h->lvl_lo.count();
+  h->info.ilu_levels_upper = h->lvl_up.count();
+}
+
 void build_ilu(Handle* h) {
   const int n = h->n;
   DBuf<int> err(&h->alloc, 1);
@@ -656,26 +672,38 @@ void build_ilu(Handle* h) {
   FAMS_REQUIRE(e == 0, FAMS_ERR_INVALID_ARG, "a row of A has no stored diagonal");
   if (!h->smoother) return;
   PhaseTimer pt(h->stream);
-  std::vector<int> lev_lo, lev_up;
-  {
-    Levels* outs[2] = {&h->lvl_lo, &h->lvl_up};
-    std::vector<int>* hls[2] = {&lev_lo, &lev_up};
-    levels_both(h, outs, hls);
+  // the schedules follow the pattern: built once, kept for new values
+  const int S = sweep_range_rows(h);
+  if (S && h->tiles.ph.empty() && !h->lvl_lo.count()) {
+    build_tiles(h, S);
+    if (!h->tiles.ph.empty()) {
+      int levels[2];
+      tile_level_counts(h, levels);
+      h->info.ilu_levels_lower = levels[0];
+      h->info.ilu_levels_upper = levels[1];
+    }
+    pt.mark("ilu tiles");
   }
+  if (h->tiles.ph.empty()) ensure_levels(h);
   pt.mark("ilu levels");
-  chunk_table(h, &h->lvl_lo);
-  chunk_table(h, &h->lvl_up);
-  if (const int S = sweep_range_rows(h)) {
-    range_table(h, lev_lo, S, &h->rng_lo);
-  }
-  pt.mark("ilu schedules");
-  h->info.ilu_levels_lower = h->lvl_lo.count();
-  h->info.ilu_levels_upper = h->lvl_up.count();
   h->ilu.reset(&h->alloc, h->nnz);
   HIPX(hipMemcpyAsync(h->ilu, h->val.get(), h->nnz * sizeof(double), hipMemcpyDeviceToDevice,
                       h->stream));
-  if (h->rng_lo.nranges > 0) {  // one launch on the range schedule
+  if (!h->tiles.ph.empty() || h->rng_lo.nranges > 0) {  // one launch on tiles or ranges
     const Ranges& L = h->rng_lo;
+    const TileSched& T = h->tiles;
+    const bool tiled = !T.ph.empty();
+    const int* rows = tiled ? T.row.get() : L.rows.get();
+    const int* seg = tiled ? T.slice.get() : L.seg.get();
+    const int* segbase = tiled ? T.tslice.get() : L.segbase.get();
+    int nranges = L.nranges, max_segs = L.max_segs;
+    if (tiled) {
+      nranges = max_segs = 0;
+      for (const TilePhase& p : T.ph) {
+        nranges += p.ntiles;
+        max_segs = std::max(max_segs, p.max_slices);
+      }
+    }
     DBuf<int> ticket(&h->alloc, 2);  // the ticket, then the wait error word
     HIPX(hipMemsetAsync(ticket, 0, 2 * sizeof(int), h->stream));
     // records of the lower schedule's positions
@@ -684,17 +712,17 @@ void build_ilu(Handle* h) {
     DBuf<unsigned char> rtg(&h->alloc, static_cast<size_t>(n) * kIluDyn);
     const IluRecs R{ri.get(), ri.get() + n, ri.get() + 2 * static_cast<size_t>(n), rav.get(),
                     ri.get() + 3 * static_cast<size_t>(n), rtg.get()};
-    LAUNCH(h, "ilu_factor", k_ilu_symbolic, blocks_for(n, kT), kT, 0, n, L.rows.get(),
-           h->rp.get(), h->ci.get(), h->diag.get(), h->val.get(), ilu_stage_width(), R);
+    LAUNCH(h, "ilu_factor", k_ilu_symbolic, blocks_for(n, kT), kT, 0, n, rows, h->rp.get(),
+           h->ci.get(), h->diag.get(), h->val.get(), ilu_stage_width(), R);
     LAUNCH(h, "ilu_factor", k_upper_arm, blocks_for(n, kT), kT, 0, n, h->rp.get(),
            h->diag.get(), h->ilu.get());
-    const size_t lds = static_cast<size_t>(L.max_segs + 1) * sizeof(int);
+    const size_t lds = static_cast<size_t>(max_segs + 1) * sizeof(int);
     FAMS_REQUIRE(lds + sizeof(double) * kIluRowW * kIluThreads <=
                      static_cast<size_t>(lds_hw_budget(h)),
                  FAMS_ERR_CAPACITY, "ILU range schedule does not fit in LDS");
     allow_lds(reinterpret_cast<const void*>(&k_ilu_ranges), lds);
-    LAUNCH(h, "ilu_factor", k_ilu_ranges, std::min(L.nranges, 2048), kIluThreads, lds, n,
-           L.nranges, L.seg.get(), L.segbase.get(), R, h->rp.get(), h->ci.get(), h->diag.get(),
+    LAUNCH(h, "ilu_factor", k_ilu_ranges, std::min(nranges, 2048), kIluThreads, lds, n,
+           nranges, seg, segbase, R, h->rp.get(), h->ci.get(), h->diag.get(),
            h->val.get(), h->ilu.get(), ticket.get(), err.get(), ticket.get() + 1,
            wait_limit(h));
     int we = 0;
@@ -726,14 +754,11 @@ void build_ilu(Handle* h) {
     h->sweep_err.reset(&h->alloc, 2);   // error bits, long waits
     HIPX(hipMemsetAsync(h->sweep_err, 0, 2 * sizeof(int), h->stream));
   }
-  if (const int cap = sweep_range_rows(h)) {
-    if (h->tiles.ph.empty()) build_tiles(h, cap);
-    if (!h->tiles.ph.empty()) {
-      if (h->precision == FAMS_PREC_MIXED) tile_values<float>(h, h->ilu32.get());
-      else tile_values<double>(h, h->ilu.get());
-    }
+  if (!h->tiles.ph.empty()) {
+    if (h->precision == FAMS_PREC_MIXED) tile_values<float>(h, h->ilu32.get());
+    else tile_values<double>(h, h->ilu.get());
     h->btiles.values = false;
-    pt.mark("ilu tiles");
+    pt.mark("ilu tile values");
   }
 }
 

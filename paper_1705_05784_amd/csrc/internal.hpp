@@ -444,6 +444,8 @@ void dense_gemm_add(Handle* h, int m, int p, int k, double alpha, const double* 
 void coarse_apply(Handle* h, const double* inv, int nc, const double* x, double* y, double* part);
 // tiles.hip: schedule of the sweeps by tiles of at most `cap` rows, the
 // factors in its order, and x = U^{-1} L^{-1} b
+void tile_level_counts(Handle* h, int out[2]);
+void ensure_levels(Handle* h);
 void build_tiles(Handle* h, int cap);
 template <class T>
 void tile_values(Handle* h, const T* lu);

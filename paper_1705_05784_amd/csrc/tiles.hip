@@ -605,6 +605,79 @@ k_tile_sweep(TileArgs<T> a) {
   }
 }
 
+// Dependency levels of a whole triangle in the schedule's order, for their
+// number (the longest chain).  A workgroup takes a tile by ticket and its
+// wavefronts take slices in turn, each row waiting for its own dependencies:
+// a level costs one published value's way through memory, and all tiles that
+// the chain allows are under way.  (Workgroups that take rows in storage order
+// hold eight planes of a 256 x 256 x 128 grid at a time, each as long as the
+// whole chain: 24 ms a triangle, this form
+// 3.2 ms.  Two wavefronts: eight poll so much that it takes 11 ms.)
+constexpr int kLevelWaves = 2;
+
+template <bool kUpper>
+__global__ void __launch_bounds__(64 * kLevelWaves)
+k_tile_levels(int ntiles, const int* slice, const int* tslice, const int* row, const int* rp,
+              const int* ci, const int* diag, int* lev, int* top, int* ticket, int* err,
+              unsigned long long limit) {
+  constexpr int D = 8;  // dependencies read together
+  __shared__ int s_c;
+  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+  int most = 0;
+  while (true) {
+    if (threadIdx.x == 0) s_c = atomicAdd(ticket, 1);
+    __syncthreads();
+    const int c = s_c;
+    __syncthreads();
+    if (c >= ntiles) break;
+    const int tile = kUpper ? ntiles - 1 - c : c;
+    const int s0 = tslice[tile], ns = tslice[tile + 1] - s0;
+    for (int k = wave; k < ns; k += kLevelWaves) {
+      const int s = s0 + (kUpper ? ns - 1 - k : k);
+      const int t = slice[s] + lane;
+      const bool on = t < slice[s + 1];
+      const int i = on ? row[t] : 0;
+      const int p1 = on ? (kUpper ? rp[i + 1] : diag[i]) : 0;
+      int p = on ? (kUpper ? diag[i] + 1 : rp[i]) : 0, L = 0;
+      const unsigned long long t0 = wall_clock64();
+      // D at a time; a wavefront vote ends the wait, so that no lane waits on
+      // another one's way out of the loop
+      while (__any(p < p1)) {
+        int dep[D], v[D];
+#pragma unroll
+        for (int q = 0; q < D; ++q) {
+          dep[q] = p + q < p1 ? ci[p + q] : -1;
+          v[q] = dep[q] < 0 ? 0 : -1;
+        }
+        bool wait = true;
+        while (__any(wait)) {
+          wait = false;
+#pragma unroll
+          for (int q = 0; q < D; ++q)
+            if (v[q] < 0)
+              v[q] = __hip_atomic_load(lev + dep[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+          for (int q = 0; q < D; ++q) wait |= v[q] < 0;
+          if (wait && (wall_clock64() - t0 > limit ||
+                       __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+            atomicOr(err, 2);
+            wait = false;
+          }
+          __builtin_amdgcn_s_sleep(1);
+        }
+#pragma unroll
+        for (int q = 0; q < D; ++q)
+          if (dep[q] >= 0) L = max(L, v[q] + 1);
+        p += D;
+      }
+      if (on) __hip_atomic_store(lev + i, L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      most = max(most, L);
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+  if (lane == 0) atomicMax(top, most);
+}
+
 }  // namespace
 
 // Schedule of the sweeps (pattern only; kept by fams_update_values).  `cap`:
@@ -752,6 +825,34 @@ void build_tiles(Handle* h, int cap) {
   state(S.st, h->precision == FAMS_PREC_MIXED ? sizeof(float) : sizeof(double));
   S.armed = false;
   HIPX(hipStreamSynchronize(h->stream));
+}
+
+// levels of the lower and the upper triangle
+void tile_level_counts(Handle* h, int out[2]) {
+  const TileSched& S = h->tiles;
+  const int n = h->n;
+  int nt = 0;
+  for (const TilePhase& p : S.ph) nt += p.ntiles;
+  DBuf<int> lev(&h->alloc, 2 * static_cast<size_t>(n)), small(&h->alloc, 6);
+  HIPX(hipMemsetAsync(lev, 0xFF, 2 * static_cast<size_t>(n) * sizeof(int), h->stream));
+  HIPX(hipMemsetAsync(small, 0, 6 * sizeof(int), h->stream));  // a triangle: top, ticket, error
+  {
+    Fork fork(h);
+    hipStream_t s0 = fork.next(), s1 = fork.next();
+    LAUNCH_ON(h, s0, "ilu_levels", k_tile_levels<false>, std::min(nt, 1024), 64 * kLevelWaves, 0, nt,
+              S.slice.get(), S.tslice.get(), S.row.get(), h->rp.get(), h->ci.get(), h->diag.get(),
+              lev.get(), small.get(), small.get() + 1, small.get() + 2, wait_limit(h));
+    LAUNCH_ON(h, s1, "ilu_levels", k_tile_levels<true>, std::min(nt, 1024), 64 * kLevelWaves, 0, nt,
+              S.slice.get(), S.tslice.get(), S.row.get(), h->rp.get(), h->ci.get(), h->diag.get(),
+              lev.get() + n, small.get() + 3, small.get() + 4, small.get() + 5, wait_limit(h));
+    fork.join();
+  }
+  int hs[6] = {};
+  HIPX(hipMemcpyAsync(hs, small.get(), sizeof(hs), hipMemcpyDeviceToHost, h->stream));
+  HIPX(hipStreamSynchronize(h->stream));
+  FAMS_REQUIRE(hs[2] == 0 && hs[5] == 0, FAMS_ERR_DEVICE, "ILU level computation did not complete");
+  out[0] = hs[0] + 1;
+  out[1] = hs[3] + 1;
 }
 
 // the factors in the schedule's order
