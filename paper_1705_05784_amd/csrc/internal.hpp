@@ -286,6 +286,24 @@ struct PhaseTimer {
 };
 
 // ---- the handle ------------------------------------------------------------
+// Two numbers that a kernel writes for the host (pinned memory), and the event
+// that says they are there: work queued behind the event runs meanwhile.
+struct HostOut {
+  double* p = nullptr;
+  hipEvent_t ev = nullptr;
+  HostOut() = default;
+  HostOut(const HostOut&) = delete;
+  HostOut& operator=(const HostOut&) = delete;
+  ~HostOut() {
+    if (ev) (void)hipEventDestroy(ev);
+    if (p) (void)hipHostFree(p);
+  }
+  void ensure() {
+    if (!p) HIPX(hipHostMalloc(reinterpret_cast<void**>(&p), 2 * sizeof(double), hipHostMallocDefault));
+    if (!ev) HIPX(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+  }
+};
+
 struct Handle {
   Allocator alloc;
   hipStream_t stream = nullptr;
@@ -337,6 +355,7 @@ struct Handle {
   BlockTiles btiles;
   DBuf<int> ilu_ticket;  // work tickets of the two sweeps
   DBuf<int> sweep_err;   // set when a bounded wait in a sweep gives up
+  HostOut host_out;  // residual norms of one right-hand side's solve
   unsigned long long wait_ticks = 0;  // bound of one wait, device wall-clock ticks
   int64_t lds_bytes = 0;              // dynamic LDS budget of the local block solves
   int64_t lds_hw_bytes = 0;           // dynamic LDS per workgroup the device allows

@@ -268,7 +268,7 @@ struct GmresState {
   double* g;    // m+1
   double* y;    // m
   double* hcol; // m+2
-  double* out;  // 2: |g_{j+1}|, h_{j+1,j}
+  double* out;  // 2: scratch scalars
 };
 
 __global__ void k_gmres_init(GmresState s, int m, const double* beta) {
@@ -280,7 +280,7 @@ __global__ void k_gmres_init(GmresState s, int m, const double* beta) {
 // (a serial chain: in global memory each rotation took a round trip).
 constexpr int kGivensLds = 64;  // columns whose rotations fit in LDS
 __global__ void __launch_bounds__(64)
-k_givens(GmresState s, int m, int j, int nb, const double* npart) {
+k_givens(GmresState s, int m, int j, int nb, const double* npart, double* host) {
   __shared__ double lds[3 * (kGivensLds + 2)];
   double sum = 0.0;
   for (int b = threadIdx.x; b < nb; b += 64) sum += npart[b];
@@ -317,8 +317,8 @@ k_givens(GmresState s, int m, int j, int nb, const double* npart) {
     const double g = s.g[j];
     s.g[j + 1] = -sg * g;
     s.g[j] = c * g;
-    s.out[0] = fabs(sg * g);
-    s.out[1] = hn;
+    host[0] = fabs(sg * g);
+    host[1] = hn;
   }
   __syncthreads();
   if (in)
@@ -461,19 +461,44 @@ void resid(Handle* h, const TV* val, const TX* x, const TB* b, TY* y, const int*
          h->rp.get(), h->ci.get(), val, x, b, y, pos);
 }
 
-// Table 1 steps 5-7 on a residual r (FP64 in, FP64 out); T = stage type
+// Table 1 steps 5-7 on a residual r (FP64 in, FP64 out); T = stage type.  The
+// coarse half (d1 = P A_c^{-1} R r) depends on r alone and touches only scratch
+// vectors, so the outer loops queue it before they wait for r's norm: the
+// device works through the host's wait and the next launches (10k unknowns:
+// 214 -> 179 us a GMRES step; the last step's share is wasted, 0.2% to 0.7% of
+// a solve).
 template <class T>
-void stage(Handle* h, const Work& k, const double* r, double* z) {
+void stage_coarse(Handle* h, const Work& k, const double* r) {
   const int n = h->n, nc = h->nc;
-  const T* pv;
-  const T* rv;
-  const T* av;
-  const T* lu;
-  const T* rT;
-  T *d1, *rh, *x, *ysc;
+  const T *pv, *rv, *rT;
+  T* d1;
   if constexpr (std::is_same<T, double>::value) {
     pv = h->p_val.get();
     rv = h->r_val.get();
+    rT = r;
+    d1 = k.d1;
+  } else {
+    pv = h->p_val32.get();
+    rv = h->r_val32.get();
+    LAUNCH(h, "cast_d2f", (k_cast<double, float>), blocks_for(n, kT), kT, 0, (int64_t)n, r,
+           k.r32);
+    rT = k.r32;
+    d1 = k.d1_32;
+  }
+  LAUNCH(h, "restrict", (k_restrict<T, T>), nc, kT, 0, nc, h->r_rp.get(), h->r_ci.get(), rv, rT,
+         k.rc);
+  coarse_apply(h, h->Ainv.get(), nc, k.rc, k.xc, k.gpart);
+  LAUNCH(h, "prolong", (k_spmv8<T, double, T>), blocks_for(n, kT / kSub), kT, 0, n,
+         h->p_rp.get(), h->p_ci.get(), pv, k.xc, d1);
+}
+
+// the rest: smoothing after stage_coarse on the same r
+template <class T>
+void stage_smooth(Handle* h, const Work& k, const double* r, double* z) {
+  const int n = h->n;
+  const T *av, *lu, *rT;
+  T *d1, *rh, *x, *ysc;
+  if constexpr (std::is_same<T, double>::value) {
     av = h->val.get();
     lu = h->ilu.get();
     rT = r;
@@ -482,23 +507,14 @@ void stage(Handle* h, const Work& k, const double* r, double* z) {
     x = k.x;
     ysc = k.y;
   } else {
-    pv = h->p_val32.get();
-    rv = h->r_val32.get();
     av = h->val32.get();
     lu = h->ilu32.get();
-    LAUNCH(h, "cast_d2f", (k_cast<double, float>), blocks_for(n, kT), kT, 0, (int64_t)n, r,
-           k.r32);
     rT = k.r32;
     d1 = k.d1_32;
     rh = k.rh32;
     x = k.x32;
     ysc = k.y32;
   }
-  LAUNCH(h, "restrict", (k_restrict<T, T>), nc, kT, 0, nc, h->r_rp.get(),
-         h->r_ci.get(), rv, rT, k.rc);
-  coarse_apply(h, h->Ainv.get(), nc, k.rc, k.xc, k.gpart);
-  LAUNCH(h, "prolong", (k_spmv8<T, double, T>), blocks_for(n, kT / kSub), kT, 0, n,
-         h->p_rp.get(), h->p_ci.get(), pv, k.xc, d1);
   if (h->smoother && !h->blk) {  // z = d1 + x is written by the upper sweep
     if (!h->tiles.ph.empty()) {
       resid<T, T, T, T>(h, av, d1, rT, h->tiles.st.x.as<T>(), h->tiles.pos.get());
@@ -531,9 +547,19 @@ void stage(Handle* h, const Work& k, const double* r, double* z) {
   }
 }
 
+void coarse_any(Handle* h, const Work& k, const double* r) {
+  if (h->precision == FAMS_PREC_MIXED) stage_coarse<float>(h, k, r);
+  else stage_coarse<double>(h, k, r);
+}
+
+void smooth_any(Handle* h, const Work& k, const double* r, double* z) {
+  if (h->precision == FAMS_PREC_MIXED) stage_smooth<float>(h, k, r, z);
+  else stage_smooth<double>(h, k, r, z);
+}
+
 void stage_any(Handle* h, const Work& k, const double* r, double* z) {
-  if (h->precision == FAMS_PREC_MIXED) stage<float>(h, k, r, z);
-  else stage<double>(h, k, r, z);
+  coarse_any(h, k, r);
+  smooth_any(h, k, r, z);
 }
 
 fams_status_t richardson(Handle* h, const Work& k, const double* q, double* p,
@@ -546,12 +572,19 @@ fams_status_t richardson(Handle* h, const Work& k, const double* q, double* p,
   fams_status_t st = FAMS_NOT_CONVERGED;
   double nr = r0;
   if (r0 == 0.0) st = FAMS_OK;
+  HostOut& host = h->host_out;
+  host.ensure();
+  if (st != FAMS_OK && it < o->max_iter) coarse_any(h, k, k.r);
   while (st != FAMS_OK && it < o->max_iter) {
-    stage_any(h, k, k.r, k.z);
+    smooth_any(h, k, k.r, k.z);
     LAUNCH(h, "axpy", k_axpy, blocks_for(n, kT), kT, 0, (int64_t)n, 1.0, k.z, p);
     resid<double, double, double, double>(h, h->val.get(), p, q, k.r);
     ++it;
-    nr = norm_host(h, k.r, n, k.part, scratch);
+    dot_into(h, k.r, k.r, n, k.part, host.p);
+    HIPX(hipEventRecord(host.ev, h->stream));
+    if (it < o->max_iter) coarse_any(h, k, k.r);  // the next iteration's, unless this is the last
+    HIPX(hipEventSynchronize(host.ev));
+    nr = std::sqrt(host.p[0]);
     if (!std::isfinite(nr) || nr > 1e8 * r0) {
       st = FAMS_DIVERGED;
       break;
@@ -574,6 +607,8 @@ fams_status_t gmres(Handle* h, const Work& k, const double* q, double* p,
   int it = 0;
   fams_status_t st = FAMS_NOT_CONVERGED;
   double beta = r0;
+  HostOut& host = h->host_out;
+  host.ensure();
   while (true) {
     if (beta <= tol) {
       st = FAMS_OK;
@@ -590,25 +625,27 @@ fams_status_t gmres(Handle* h, const Work& k, const double* q, double* p,
     LAUNCH(h, "scale", k_scale_by, blocks_for(n, kT), kT, 0, n, k.r, k.gs.hcol + m + 1, k.V);
     LAUNCH(h, "gmres_init", k_gmres_init, 1, 1, 0, k.gs, m, k.gs.hcol + m + 1);
     int kk = 0;
+    coarse_any(h, k, k.V);
     for (int j = 0; j < m; ++j) {
       double* vj = k.V + j * n;
       double* zj = k.Z + j * n;
-      stage_any(h, k, vj, zj);
+      smooth_any(h, k, vj, zj);
       LAUNCH(h, "spmv", (k_spmv8<double, double, double>), blocks_for(n, kT / kSub), kT, 0,
              (int)n, h->rp.get(), h->ci.get(), h->val.get(), zj, k.w);
       orthogonalise(h, k, n, j + 1);
-      LAUNCH(h, "givens", k_givens, 1, 64, 0, k.gs, m, j, gs_blocks(n), k.gs_npart);
-      double est_hn[2];
-      HIPX(hipMemcpyAsync(est_hn, k.gs.out, 2 * sizeof(double), hipMemcpyDeviceToHost,
-                          h->stream));
-      HIPX(hipStreamSynchronize(h->stream));
+      LAUNCH(h, "givens", k_givens, 1, 64, 0, k.gs, m, j, gs_blocks(n), k.gs_npart,
+             host.p);
+      HIPX(hipEventRecord(host.ev, h->stream));
+      if (j + 1 < m && it + 1 < o->max_iter) {  // the next step's start, unless this is the last
+        LAUNCH(h, "scale", k_scale_by, blocks_for(n, kT), kT, 0, n, k.w, k.gs.hcol + j + 1,
+               vj + n);
+        coarse_any(h, k, vj + n);
+      }
+      HIPX(hipEventSynchronize(host.ev));
       ++it;
       kk = j + 1;
-      if (est_hn[0] <= tol || it >= o->max_iter || !(est_hn[1] > 0.0) ||
-          !std::isfinite(est_hn[0]))
+      if (host.p[0] <= tol || it >= o->max_iter || !(host.p[1] > 0.0) || !std::isfinite(host.p[0]))
         break;
-      LAUNCH(h, "scale", k_scale_by, blocks_for(n, kT), kT, 0, n, k.w, k.gs.hcol + j + 1,
-             k.V + (j + 1) * n);
     }
     LAUNCH(h, "backsolve", k_backsolve, 1, 1, 0, k.gs, m, kk);
     LAUNCH(h, "maxpy", k_maxpy, blocks_for(n, kT), kT, 0, n, kk, k.Z, n, k.gs.y, 1.0, p);
