@@ -262,10 +262,11 @@ k_sweep_upper(const int* rows, const int* chunk, int nchunks, const int* rp, con
   }
 }
 
-// ILU(0) factorisation in one launch on the lower sweep's range schedule
-// (the factorisation of row i needs exactly the rows its lower triangle
-// refers to).  A workgroup takes ranges in ticket order and walks a range
-// level by level with a barrier between levels.  Other rows read only the
+// ILU(0) factorisation in one launch on the sweeps' tiles, or on ranges of
+// consecutive rows where there are none (the factorisation of row i needs
+// exactly the rows its lower triangle refers to).  A workgroup takes tiles in
+// ticket order and walks a tile slice by slice (a range level by level) with a
+// barrier after each.  Other rows read only the
 // upper part of a pivot row (its diagonal and the entries right of it), so
 // that part is published entry by entry with the value itself as the ready
 // flag, as in the sweeps: every upper entry of lu starts as the sentinel
@@ -570,8 +571,6 @@ __global__ void k_d2f_ilu(int64_t n, const double* a, float* b) {
   if (i < n) b[i] = static_cast<float>(a[i]);
 }
 
-// rows per range of the range sweeps: FAMS_ILU_RANGE (0 selects the
-// level-chunk sweeps), default 8192
 // widest row the factorisation stages in LDS (0: every row entry by entry)
 int ilu_stage_width() {
   int w = kIluRowW;
@@ -579,6 +578,8 @@ int ilu_stage_width() {
   return std::max(0, std::min(w, kIluRowW));
 }
 
+// most rows of a tile or range: FAMS_ILU_RANGE (0 selects the level-chunk
+// sweeps and the factorisation by levels), default 8192
 int sweep_range_rows(Handle* h) {
   (void)h;
   int S = 8192;
@@ -587,7 +588,7 @@ int sweep_range_rows(Handle* h) {
   return std::min(S, 16384);
 }
 
-// range schedule of one sweep from the rows' global dependency levels: inside
+// range schedule of the factorisation from the rows' global dependency levels: inside
 // a range, rows of equal level are independent and every dependency inside
 // the range has a lower level, so a workgroup can take the range level by
 // level with a barrier between levels (counting sort per range, host side)

@@ -146,7 +146,6 @@ def traffic(fetch_db, write_db, copy_bytes, out_json, source_digest, launch_name
 # library kernel symbols -> the launch names used by the library's own timers
 LAUNCH_NAMES = {
     "k_local_solve<float, float>": "local_solve",
-    "k_sweep_ranges<float, false>": "ilu_lower", "k_sweep_ranges<float, true>": "ilu_upper",
     "k_sweep_lower<float>": "ilu_lower", "k_sweep_upper<float>": "ilu_upper",
     # lock-step kernels of the precision form with 32 right-hand sides
     "k_bsweep<float, false, 32>": "bilu_lower", "k_bsweep<float, true, 32>": "bilu_upper",
@@ -156,12 +155,18 @@ LAUNCH_NAMES = {
     "k_bspmv_ell<float, double, float, float, 32, false>": "bprolong",
     "k_brestrict<float, float, 32>": "brestrict", "k_bcoarse_mfma<32>": "bcoarse",
     "k_bcast<double, float>": "bcast_d2f",
-    "k_gemm_mfma128": "gemm_mfma",
+    "k_gemm_mfma128*": "gemm_mfma",
     # the Gram-Schmidt passes, one instantiation per basis size bucket
     "k_bmaxpy_mdot<32,*": "bmaxpy_mdot", "k_bmaxpy_norm<32,*": "bmaxpy_norm",
     "k_bmdot<32,*": "bmdot", "k_bmdot<32, 1>": "bdot",
     "k_dcgs_dots<32,*": "bgs_dots", "k_dcgs_update<32,*": "bgs_update",
 }
+# the tiled sweeps, one instantiation per number of dependencies in a record
+for _c in (3, 4, 8):
+    for _up, _name in (("false", "lower"), ("true", "upper")):
+        LAUNCH_NAMES[f"k_tile_sweep<float, {_c}, {_up}>"] = f"ilu_{_name}"
+        for _over in ("false", "true"):
+            LAUNCH_NAMES[f"k_btile_sweep<float, 32, {_c}, {_up}, {_over}>"] = f"bilu_{_name}"
 
 
 def _main(argv):
