@@ -675,14 +675,15 @@ void ensure_workspace(Handle* h, int restart) {
   int m = std::max(restart, 1);
   size_t need = static_cast<size_t>(7 + 2 * m + 1);
   if (h->wk_vectors >= need) return;
+  h->wk_vectors = 0;  // none until every buffer is there
   h->wk.reset(&h->alloc, need * static_cast<size_t>(h->n));
-  h->wk_vectors = need;
   h->red.reset(&h->alloc, static_cast<size_t>(kRedBlocks) * (m + 2) + 16);
   h->hred.reset(&h->alloc, 2 * static_cast<size_t>(h->nc) + static_cast<size_t>(m + 1) * m +
                                6 * static_cast<size_t>(m) + 16);
   if (h->precision == FAMS_PREC_MIXED) h->wk32.reset(&h->alloc, 5 * static_cast<size_t>(h->n));
   const size_t nch = (static_cast<size_t>(h->nc) + 63) / 64;   // coarse GEMV column chunks
-  if (h->gpart.size() < nch * h->nc) h->gpart.reset(&h->alloc, nch * h->nc);
+  if (!h->gpart.get()) h->gpart.reset(&h->alloc, nch * h->nc);
+  h->wk_vectors = need;
 }
 
 fams_status_t solve_one(Handle* h, const double* q, double* p, const fams_solve_opts_t* o,
