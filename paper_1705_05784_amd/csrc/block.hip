@@ -1261,7 +1261,7 @@ template <class TV>
 const TV* ell_vals(Handle* h, EllMat& e, const int* rp, const int* ci, const double* val,
                    const float* val32) {
   const int n = h->n;
-  if (!e.col.get()) {
+  if (!e.ovf.get()) {  // the last of the two: a refused allocation leaves it empty
     e.col.reset(&h->alloc, static_cast<size_t>(n) * kEll);
     e.ovf.reset(&h->alloc, 2 * static_cast<size_t>(n));
     LAUNCH(h, "bell", k_ell_cols, blocks_for(n, 256), 256, 0, n, rp, ci, e.col.get(),

@@ -51,7 +51,7 @@ def _rhs(n, k):
     return (q if k > 1 else q[0]).cuda()
 
 
-def _refuse_each(nrhs, smoother=1, precision=0, rule=None):
+def _refuse_each(nrhs, smoother=1, precision=0, rule=None, most=None):
     """The first solve of a new handle with its k-th allocation refused, for
     every k (or with what `rule(k)` refuses), then a second one with nothing
     refused; returns how many first solves went through."""
@@ -65,7 +65,7 @@ def _refuse_each(nrhs, smoother=1, precision=0, rule=None):
     g.close()
     assert count > 0
     through = 0
-    for k in range(count):
+    for k in range(min(count, most or count)):
         print(f"[refusals] nrhs {nrhs} smoother {smoother} precision {precision} refused {k}",
               flush=True)
         hook.arm(None)
@@ -86,3 +86,20 @@ def _refuse_each(nrhs, smoother=1, precision=0, rule=None):
 @pytest.mark.parametrize("precision", [0, 1])
 def test_single_solve(precision):
     assert _refuse_each(1, precision=precision) == 0
+
+
+def test_fixed_width_matrices():
+    """Lock-step solves: the overflow table of A, then of P (two ints a row)."""
+    hook = Hook()
+    g = _solver(hook)
+    n = g.n
+    g.close()
+
+    def rule(k):
+        seen = [0]
+
+        def refuse(i, nbytes):
+            seen[0] += nbytes == 8 * n
+            return nbytes == 8 * n and seen[0] == k % 2 + 1
+        return refuse
+    assert _refuse_each(4, rule=rule, most=2) == 0
