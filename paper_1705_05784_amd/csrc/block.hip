@@ -1219,26 +1219,32 @@ void free_block_workspace(Handle* h) {
     }
 }
 
-void prepare_sweeps(Handle* h, int K) {
+// What the sweeps of groups of K keep beside the work space: the tiles' records
+// and published values, or (plain, and where no tiles serve) the level chunks,
+// which take a tenth of that.
+void prepare_sweeps(Handle* h, int K, bool plain) {
   if (!h->smoother) return;
-  for (Handle* g : {h, h->blk.get()})
-    if (g && !block_tiles_prepare(g, K)) ensure_levels(g);
+  for (Handle* g : {h, h->blk.get()}) {
+    if (!g) continue;
+    if (plain) g->btiles = BlockTiles();
+    if (plain || !block_tiles_prepare(g, K)) ensure_levels(g);
+  }
 }
 
 // all or nothing: a failed allocation leaves no work space (bK = 0)
-void ensure_block_workspace(Handle* h, int K, int m) {
+void ensure_block_workspace(Handle* h, int K, int m, bool plain) {
   if (!h->tiling_known) {
     h->tiling = infer_tiling(h);
     h->tiling_known = true;
     h->info.tiled_rows = h->tiling.sy ? h->tiling.nm : 0;
   }
-  if (h->bK == K && h->bm >= m && h->bwk.get()) {
-    prepare_sweeps(h, K);  // the factors may be new
+  if (h->bK == K && h->bm >= m && h->bplain == plain) {
+    prepare_sweeps(h, K, plain);  // the factors may be new
     return;
   }
   free_block_workspace(h);
   try {
-    prepare_sweeps(h, K);
+    prepare_sweeps(h, K, plain);
     const size_t nk = static_cast<size_t>(h->n) * K;
     h->bwk.reset(&h->alloc, block_vectors(m) * nk);
     if (h->precision == FAMS_PREC_MIXED) h->bwk32.reset(&h->alloc, 6 * nk);
@@ -1253,6 +1259,7 @@ void ensure_block_workspace(Handle* h, int K, int m) {
   }
   h->bK = K;
   h->bm = m;
+  h->bplain = plain;
 }
 
 // the fixed-width form of the CSR matrix (rp, ci, val, val32) with values
@@ -1593,9 +1600,9 @@ void block_richardson(Handle* h, const BWork& k, int nr, const fams_solve_opts_t
 
 template <int K>
 void solve_group(Handle* h, const double* q, double* p, int nr, const fams_solve_opts_t* o,
-                 fams_info_t* info) {
+                 fams_info_t* info, bool plain) {
   const int m = o->outer == FAMS_GMRES ? o->restart : 1;
-  ensure_block_workspace(h, K, m);
+  ensure_block_workspace(h, K, m, plain);
   BWork k = block_work(h, K, m);
   const int n = h->n;
   const int64_t nk = k.nk;
@@ -1642,6 +1649,7 @@ fams_status_t solve_block(Handle* h, const double* q, double* p, int nrhs,
   // the widest group (up to 32 right-hand sides, no wider than nrhs needs)
   // whose work space fits in the device memory
   int K = 32;
+  bool plain = false;  // without the tiles' buffers, where these do not fit
   while (K > 2 && K / 2 >= nrhs) K /= 2;
   size_t free_b = 0, total_b = 0;
   HIPX(hipMemGetInfo(&free_b, &total_b));
@@ -1654,15 +1662,16 @@ fams_status_t solve_block(Handle* h, const double* q, double* p, int nrhs,
   } else {
     // an allocation hook may hold memory that the device does not count as
     // free (a caching allocator): ask the hook for the widest work space and
-    // halve the group while it refuses
+    // halve the group while it refuses; a pair last without the tiles
     while (K > 2 && block_bytes(h, K, m) > total_b) K /= 2;
     for (;;) {
       try {
-        ensure_block_workspace(h, K, m);
+        ensure_block_workspace(h, K, m, plain);
         break;
       } catch (const Error& e) {
-        if (e.status != FAMS_ERR_OOM || K == 2) throw;
-        K /= 2;
+        if (e.status != FAMS_ERR_OOM || plain) throw;
+        if (K > 2) K /= 2;
+        else plain = true;
       }
     }
   }
@@ -1674,11 +1683,11 @@ fams_status_t solve_block(Handle* h, const double* q, double* p, int nrhs,
     const double* qg = q + r0 * n;
     double* pg = p + r0 * n;
     switch (K) {
-      case 2: solve_group<2>(h, qg, pg, nr, o, inf); break;
-      case 4: solve_group<4>(h, qg, pg, nr, o, inf); break;
-      case 8: solve_group<8>(h, qg, pg, nr, o, inf); break;
-      case 16: solve_group<16>(h, qg, pg, nr, o, inf); break;
-      default: solve_group<32>(h, qg, pg, nr, o, inf); break;
+      case 2: solve_group<2>(h, qg, pg, nr, o, inf, plain); break;
+      case 4: solve_group<4>(h, qg, pg, nr, o, inf, plain); break;
+      case 8: solve_group<8>(h, qg, pg, nr, o, inf, plain); break;
+      case 16: solve_group<16>(h, qg, pg, nr, o, inf, plain); break;
+      default: solve_group<32>(h, qg, pg, nr, o, inf, plain); break;
     }
     for (int r = 0; r < nr; ++r)
       if (inf[r].status > worst) worst = static_cast<fams_status_t>(inf[r].status);

@@ -510,7 +510,8 @@ size_t rec_bytes(const TilePhase& p) {
 }  // namespace
 
 // The schedule's part for lock-step sweeps and the published values of
-// groups of K, on first use; false: these sizes are not served.
+// groups of K, on first use; false: these sizes are not served.  A refused
+// allocation leaves what is there in use, and the rest to the next call.
 bool block_tiles_prepare(Handle* h, int K) {
   TileSched& S = h->tiles;
   BlockTiles& B = h->btiles;
@@ -522,43 +523,48 @@ bool block_tiles_prepare(Handle* h, int K) {
     B.K = 0;
     return false;
   }
-  if (!B.sno.get()) {
+  if (!B.built) {
     int nt = 0;
     for (const TilePhase& p : S.ph) nt += p.ntiles;
-    B.sno.reset(A, n);
-    B.tile_of.reset(A, n);
-    B.lo.reset(A, n);
-    B.up.reset(A, n);
-    LAUNCH(h, "btiles", k_slice_numbers, nt, 64, 0, S.tslice.get(), S.slice.get(), B.sno.get(),
-           B.tile_of.get());
+    BlockTiles N;
+    N.sno.reset(A, n);
+    N.tile_of.reset(A, n);
+    N.lo.reset(A, n);
+    N.up.reset(A, n);
+    N.ticket.reset(A, 4 * kTicketStride);
+    LAUNCH(h, "btiles", k_slice_numbers, nt, 64, 0, S.tslice.get(), S.slice.get(), N.sno.get(),
+           N.tile_of.get());
     DBuf<int> ml(A, n + 1), mu(A, n + 1), sc(A, n + 1);
     HIPX(hipMemsetAsync(ml, 0, (n + 1) * sizeof(int), h->stream));
     HIPX(hipMemsetAsync(mu, 0, (n + 1) * sizeof(int), h->stream));
     for (const TilePhase& p : S.ph)
       LAUNCH(h, "btiles", k_bmarks, blocks_for(p.row1 - p.row0, kT), kT, 0, p.row0, p.row1, p.row0,
              p.row1, p.C, S.row.get(), S.pos.get(), h->rp.get(), h->ci.get(), h->diag.get(),
-             Near{B.sno.get(), B.tile_of.get()}, ml.get(), mu.get());
+             Near{N.sno.get(), N.tile_of.get()}, ml.get(), mu.get());
     int cnt[2];
     for (int u = 0; u < 2; ++u) {
       DBuf<int>& m = u ? mu : ml;
       exclusive_scan_i32(h, m, sc, n + 1);
       LAUNCH(h, "btiles", k_bslots, blocks_for(n, kT), kT, 0, n, m.get(), sc.get(),
-             (u ? B.up : B.lo).get());
+             (u ? N.up : N.lo).get());
       HIPX(hipMemcpyAsync(&cnt[u], sc.get() + n, sizeof(int), hipMemcpyDeviceToHost, h->stream));
     }
     HIPX(hipStreamSynchronize(h->stream));
-    B.nlo = cnt[0];
-    B.nup = cnt[1];
-    B.ticket.reset(A, 4 * kTicketStride);
-    B.armed = false;
+    N.nlo = cnt[0];
+    N.nup = cnt[1];
+    N.built = true;
+    B = std::move(N);
   }
   if (!B.values) {
     size_t bytes = 0;
     for (const TilePhase& p : S.ph)
       bytes += (mixed ? rec_bytes<float>(p) : rec_bytes<double>(p)) * (p.row1 - p.row0);
-    if (B.lrec.size() != bytes) {
-      B.lrec.reset(A, bytes);
-      B.urec.reset(A, bytes);
+    if (!B.urec.get()) {
+      Bytes l, u;
+      l.reset(A, bytes);
+      u.reset(A, bytes);
+      B.lrec = std::move(l);
+      B.urec = std::move(u);
     }
     size_t off = 0;
     for (const TilePhase& p : S.ph) {

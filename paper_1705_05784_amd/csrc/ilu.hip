@@ -646,16 +646,22 @@ void chunk_table(Handle* h, Levels* L) {
 
 // level order of both triangles, where no tiles serve: the level-chunk sweeps
 // and the factorisation by ranges (or by levels)
+// (built aside: a solve may come here, and again after a refused allocation)
 void ensure_levels(Handle* h) {
   if (h->lvl_lo.count()) return;
   std::vector<int> lev_lo, lev_up;
-  Levels* outs[2] = {&h->lvl_lo, &h->lvl_up};
+  Levels lo, up;
+  Ranges rng;
+  Levels* outs[2] = {&lo, &up};
   std::vector<int>* hls[2] = {&lev_lo, &lev_up};
   levels_both(h, outs, hls);
-  chunk_table(h, &h->lvl_lo);
-  chunk_table(h, &h->lvl_up);
+  chunk_table(h, &lo);
+  chunk_table(h, &up);
   if (const int S = sweep_range_rows(h))
-    if (h->tiles.ph.empty()) range_table(h, lev_lo, S, &h->rng_lo);
+    if (h->tiles.ph.empty()) range_table(h, lev_lo, S, &rng);
+  h->lvl_lo = std::move(lo);
+  h->lvl_up = std::move(up);
+  h->rng_lo = std::move(rng);
   h->info.ilu_levels_lower = h->lvl_lo.count();
   h->info.ilu_levels_upper = h->lvl_up.count();
 }

@@ -67,8 +67,8 @@ class DBuf {
   void reset(Allocator* a, size_t n) {
     free();
     a_ = a;
-    n_ = n;
     p_ = n ? static_cast<T*>(a->alloc(n * sizeof(T))) : nullptr;
+    n_ = n;  // empty when the allocation throws
   }
   void free() {
     if (p_ && a_) a_->release(p_, n_ * sizeof(T));
@@ -267,12 +267,15 @@ struct TileSched {
 
 // The schedule's part for lock-step sweeps (btiles.hip), built on first use:
 // slice and tile of every position, the slots of published rows (lower,
-// upper), the rows' records, and the published values of groups of K.
+// upper), the rows' records, and the published values of groups of K.  Each
+// part is built aside and moved here when all of its allocations succeeded:
+// `built` the schedule, `values` the records of the present factors, K the
+// published values (0: none).
 struct BlockTiles {
   DBuf<int> sno, tile_of, lo, up, ticket;
-  int nlo = 0, nup = 0, K = 0;  // K = 0: no values allocated
+  int nlo = 0, nup = 0, K = 0;
   Bytes lrec, urec, hl, hu;
-  bool values = false, armed = false;
+  bool built = false, values = false, armed = false;
 };
 
 // Host phase timer: with FAMS_SETUP_TIMING set, mark() synchronises the
@@ -387,6 +390,7 @@ struct Handle {
   DBuf<double> bsmall;  // per-right-hand-side GMRES state and scalars
   DBuf<double> bpart;   // partial sums of the coarse block product
   int bK = 0, bm = 0;
+  bool bplain = false;  // sized for the sweeps over level chunks (no tiles)
   RowTiling tiling;     // visiting order of the lock-step products with A
   bool tiling_known = false;
   // A and P in fixed width for the lock-step products

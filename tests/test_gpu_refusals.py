@@ -103,3 +103,45 @@ def test_fixed_width_matrices():
             return nbytes == 8 * n and seen[0] == k % 2 + 1
         return refuse
     assert _refuse_each(4, rule=rule, most=2) == 0
+
+
+@pytest.mark.parametrize("smoother,precision", [(1, 0), (1, 1), (2, 0)])
+def test_lockstep_solve(smoother, precision):
+    """Each allocation by itself: groups narrow and the solve goes on where
+    the work space and the sweeps' part of the schedule are concerned."""
+    assert _refuse_each(7, smoother, precision) > 10
+
+
+@pytest.mark.parametrize("smoother,precision", [(1, 0), (1, 1), (2, 0)])
+def test_lockstep_solve_without_room(smoother, precision):
+    """Everything from the k-th allocation on: no first solve has room."""
+    assert _refuse_each(4, smoother, precision, lambda k: lambda i, nbytes: i >= k) == 0
+
+
+@pytest.mark.parametrize("smoother,precision", [(1, 0), (1, 1), (2, 0)])
+def test_pair_without_records(smoother, precision):
+    """A pair of right-hand sides goes on without the tiles' records (48 to
+    128 bytes a row): the sweeps take the level chunks then, as they do where
+    the block vectors pass 4 GiB."""
+    hook = Hook()
+    g = _solver(hook, smoother, precision)
+    q = _rhs(g.n, 2)
+    ref = g.solve(q, **ONCE)[0].cpu().numpy()
+    g.close()
+    hook = Hook()
+    g = _solver(hook, smoother, precision)
+    refused = []
+
+    def rule(i, nbytes):   # the second of the two arrays, allocated one after the other
+        if 48 * g.n <= nbytes <= 128 * g.n and hook.sizes[-2:] == [nbytes, nbytes]:
+            refused.append(nbytes)
+            return True
+        return False
+    hook.arm(rule)
+    for k in range(2):
+        p = g.solve(q, **ONCE)[0].cpu().numpy()
+        assert np.abs(p - ref).max() <= (1e-3 if precision else 1e-10) * np.abs(ref).max()
+        assert len(refused) == k + 1
+    hook.arm(None)
+    assert np.array_equal(g.solve(q, **ONCE)[0].cpu().numpy(), ref)
+    g.close()
