@@ -155,7 +155,9 @@ k_run_levels(int row0, int n, const int* rp, const int* ci, int* lev, int* ticke
 
 // keys of rows in tiles of S consecutive rows.  A level that does not fit its
 // bits, or an upper column without its mirror whose level is not higher (a
-// pattern that is not symmetric), sets *bad: no schedule for both sweeps.
+// pattern that is not symmetric), sets *bad: no schedule for both sweeps.  The
+// tile of such a key stays right (level 0), as everything up to the host's
+// look at *bad indexes by it.
 __global__ void k_run_keys(int row0, int n, int S, int tile0, int lb, const int* rp, const int* ci,
                            const int* lev, int* key, int* row, int* bad) {
   const int i = row0 + blockIdx.x * blockDim.x + threadIdx.x;
@@ -164,7 +166,7 @@ __global__ void k_run_keys(int row0, int n, int S, int tile0, int lb, const int*
   bool no = L < 0 || L >> lb != 0;
   for (int p = rp[i + 1] - 1; p >= rp[i] && ci[p] > i; --p) no |= lev[ci[p]] <= L;
   if (no) *bad = 1;
-  key[i] = (tile0 + (i - row0) / S) << lb | L;
+  key[i] = (tile0 + (i - row0) / S) << lb | (no ? 0 : L);
   row[i] = i;
 }
 
