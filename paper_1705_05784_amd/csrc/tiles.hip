@@ -157,7 +157,7 @@ k_run_levels(int row0, int n, const int* rp, const int* ci, int* lev, int* ticke
 // bits, or an upper column without its mirror whose level is not higher (a
 // pattern that is not symmetric), sets *bad: no schedule for both sweeps.  The
 // tile of such a key stays right (level 0), as everything up to the host's
-// look at *bad indexes by it.
+// look at *bad indexes by it; run_keys_on_host finds another order then.
 __global__ void k_run_keys(int row0, int n, int S, int tile0, int lb, const int* rp, const int* ci,
                            const int* lev, int* key, int* row, int* bad) {
   const int i = row0 + blockIdx.x * blockDim.x + threadIdx.x;
@@ -480,7 +480,8 @@ k_tile_sweep(TileArgs<T> a) {
     auto fetch_outside = [&](E& e) {
 #pragma unroll
       for (int q = 0; q < C; ++q)
-        e.raw[q] = buffer_get<U, kCoherent>(outside, e.c[q] < 0 ? ~e.c[q] * S : kNowhere);
+        e.raw[q] = buffer_get<U, kCoherent>(
+            outside, e.c[q] < 0 ? static_cast<int>(static_cast<unsigned>(~e.c[q]) * S) : kNowhere);
     };
     E e[G], nx[G];
     const int ng = (ns + G - 1) / G;
@@ -680,6 +681,50 @@ k_tile_levels(int ntiles, const int* slice, const int* tslice, const int* row, c
   if (lane == 0) atomicMax(top, most);
 }
 
+// The keys of k_run_keys for any pattern, on the host: the longest path over
+// the couplings of either triangle, in either direction, which increases along
+// every coupling by itself; inside a tile its rank among the tile's levels, so
+// that it fits where the level would not.  One pass over the rows' columns:
+// lower ones are final when a row is reached, upper ones are pushed ahead.
+// false: more ranks than the key has bits for.
+bool run_keys_on_host(Handle* h, int row0, int S, int tile0, int lb, int* key) {
+  const int m = h->n - row0;
+  std::vector<int> rp(m + 1);
+  HIPX(hipMemcpyAsync(rp.data(), h->rp.get() + row0, rp.size() * sizeof(int),
+                      hipMemcpyDeviceToHost, h->stream));
+  HIPX(hipStreamSynchronize(h->stream));
+  const int p0 = rp[0];
+  std::vector<int> ci(rp[m] - p0), lev(m, 0), out(m), ranks;
+  HIPX(hipMemcpyAsync(ci.data(), h->ci.get() + p0, ci.size() * sizeof(int),
+                      hipMemcpyDeviceToHost, h->stream));
+  HIPX(hipStreamSynchronize(h->stream));
+  for (int i = 0; i < m; ++i) {
+    const int* c = ci.data() + (rp[i] - p0);
+    const int* e = ci.data() + (rp[i + 1] - p0);
+    int L = lev[i];
+    for (const int* p = c; p < e; ++p)
+      if (*p >= row0 && *p - row0 < i) L = std::max(L, lev[*p - row0] + 1);
+    lev[i] = L;
+    for (const int* p = c; p < e; ++p)
+      if (*p - row0 > i) lev[*p - row0] = std::max(lev[*p - row0], L + 1);
+  }
+  for (int a = 0; a < m; a += S) {
+    const int b = std::min(m, a + S);
+    ranks.assign(lev.begin() + a, lev.begin() + b);
+    std::sort(ranks.begin(), ranks.end());
+    ranks.erase(std::unique(ranks.begin(), ranks.end()), ranks.end());
+    if (ranks.size() > size_t(1) << lb) return false;
+    for (int i = a; i < b; ++i)
+      out[i] = (tile0 + a / S) << lb |
+               static_cast<int>(std::lower_bound(ranks.begin(), ranks.end(), lev[i]) -
+                                ranks.begin());
+  }
+  HIPX(hipMemcpyAsync(key + row0, out.data(), out.size() * sizeof(int), hipMemcpyHostToDevice,
+                      h->stream));
+  HIPX(hipStreamSynchronize(h->stream));
+  return true;
+}
+
 }  // namespace
 
 // Schedule of the sweeps (pattern only; kept by fams_update_values).  `cap`:
@@ -689,7 +734,8 @@ void build_tiles(Handle* h, int cap) {
   TileSched& S = h->tiles;
   const int n = h->n, nm = h->nm;
   S.clear();
-  if (n >= 1 << 28) return;  // buffer offsets of 32 bits; the level-chunk sweeps take over
+  const double vec = n * (h->precision == FAMS_PREC_MIXED ? 4.0 : 8.0);
+  if (vec >= 4294967296.0 - 512) return;  // buffer offsets of 32 bits: level-chunk sweeps
   // the grid behind the matrix rows
   GridShape g{0, 0, 0};
   if (nm >= 4) {
@@ -745,6 +791,7 @@ void build_tiles(Handle* h, int cap) {
   S.tslice.reset(A, nt + 1);
   DBuf<int> key(A, n), rows(A, n), keys(A, n), tstart(A, nt + 1), cnt(A, nt + 1), small(A, 8);
   HIPX(hipMemsetAsync(small, 0, 8 * sizeof(int), h->stream));
+  int total = 0, hs[8] = {};
   for (TilePhase& p : S.ph) {
     if (p.boxes) {
       LAUNCH(h, "tiles", k_box_keys, blocks_for(nm, kT), kT, 0, nm, b, lb, key.get(), rows.get());
@@ -758,27 +805,39 @@ void build_tiles(Handle* h, int cap) {
     LAUNCH(h, "tiles", k_run_keys, blocks_for(m, kT), kT, 0, p.row0, n, run, p.tile0, lb,
            h->rp.get(), h->ci.get(), keys.get(), key.get(), rows.get(), small.get() + 6);
   }
-  sort_pairs_i32(h, key, keys, rows, S.row, n, 31);
-  LAUNCH(h, "tiles", k_tile_starts, blocks_for(n, kT), kT, 0, n, nt, lb, keys.get(), S.row.get(),
-         S.pos.get(), tstart.get());
-  // slices: counts per tile, then starts; maxima per phase
-  HIPX(hipMemsetAsync(cnt, 0, (nt + 1) * sizeof(int), h->stream));
-  for (size_t k = 0; k < S.ph.size(); ++k) {
-    TilePhase& p = S.ph[k];
-    LAUNCH(h, "tiles", k_tile_slices, p.ntiles, 64, 0, tstart.get() + p.tile0, keys.get(),
-           cnt.get() + p.tile0, static_cast<int*>(nullptr), small.get() + k);
-    LAUNCH(h, "tiles", k_most_deps, blocks_for(p.row1 - p.row0, kT), kT, 0, p.row0, p.row1,
-           h->rp.get(), h->ci.get(), small.get() + 2 + k);
-  }
-  exclusive_scan_i32(h, cnt, S.tslice, nt + 1);
-  int total = 0, hs[8] = {};
-  HIPX(hipMemcpyAsync(&total, S.tslice.get() + nt, sizeof(int), hipMemcpyDeviceToHost, h->stream));
-  HIPX(hipMemcpyAsync(hs, small.get(), sizeof(hs), hipMemcpyDeviceToHost, h->stream));
-  HIPX(hipStreamSynchronize(h->stream));
+  auto order = [&]() {  // positions, tiles and slices of the keys
+    sort_pairs_i32(h, key, keys, rows, S.row, n, 31);
+    LAUNCH(h, "tiles", k_tile_starts, blocks_for(n, kT), kT, 0, n, nt, lb, keys.get(), S.row.get(),
+           S.pos.get(), tstart.get());
+    // slices: counts per tile, then starts; maxima per phase
+    HIPX(hipMemsetAsync(cnt, 0, (nt + 1) * sizeof(int), h->stream));
+    for (size_t k = 0; k < S.ph.size(); ++k) {
+      TilePhase& p = S.ph[k];
+      LAUNCH(h, "tiles", k_tile_slices, p.ntiles, 64, 0, tstart.get() + p.tile0, keys.get(),
+             cnt.get() + p.tile0, static_cast<int*>(nullptr), small.get() + k);
+      LAUNCH(h, "tiles", k_most_deps, blocks_for(p.row1 - p.row0, kT), kT, 0, p.row0, p.row1,
+             h->rp.get(), h->ci.get(), small.get() + 2 + k);
+    }
+    exclusive_scan_i32(h, cnt, S.tslice, nt + 1);
+    HIPX(hipMemcpyAsync(&total, S.tslice.get() + nt, sizeof(int), hipMemcpyDeviceToHost,
+                        h->stream));
+    HIPX(hipMemcpyAsync(hs, small.get(), sizeof(hs), hipMemcpyDeviceToHost, h->stream));
+    HIPX(hipStreamSynchronize(h->stream));
+  };
+  order();
   FAMS_REQUIRE(hs[5] == 0, FAMS_ERR_DEVICE, "ILU level computation did not complete");
-  if (hs[6]) {  // no order that serves both sweeps: the level-chunk sweeps take over
-    S.clear();
-    return;
+  if (hs[6]) {
+    // The device's levels are no order for both sweeps.  (60 x 50 x 30 cells
+    // and 30 plates in FP64, 7% more couplings stored on one side: a two-stage step
+    // takes 2000 us by level chunks and 377 us by the tiles of this order; the
+    // setup, with its LU local solves, 136.5 and 140.1 ms.)
+    const TilePhase& p = S.ph.back();
+    if (!run_keys_on_host(h, p.row0, run, p.tile0, lb, key.get())) {
+      S.clear();
+      return;
+    }
+    HIPX(hipMemsetAsync(small, 0, 8 * sizeof(int), h->stream));
+    order();
   }
   S.slice.reset(A, total + 1);
   HIPX(hipMemcpyAsync(S.slice.get() + total, tstart.get() + nt, sizeof(int),
