@@ -1620,17 +1620,7 @@ void solve_group(Handle* h, const double* q, double* p, int nr, const fams_solve
   else block_richardson<K>(h, k, nr, o, rs);
   LAUNCH(h, "bunpack", k_unpack<K>, blocks_for(n, kPackRows), kT, 0, n, nr, k.p, p);
   HIPX(hipStreamSynchronize(h->stream));
-  int e = 0;
-  for (Handle* g : {h, h->blk.get()}) {
-    if (!g || !g->sweep_err.get()) continue;
-    int eg[2] = {};
-    HIPX(hipMemcpyAsync(eg, g->sweep_err.get(), sizeof(eg), hipMemcpyDeviceToHost, h->stream));
-    HIPX(hipStreamSynchronize(h->stream));
-    e |= eg[0];
-    if (eg[0]) g->btiles.armed = false;
-    h->info.long_waits += eg[1];
-  }
-  FAMS_REQUIRE(e == 0, FAMS_ERR_DEVICE, "ILU(0) sweep: a dependency wait exceeded its bound");
+  check_sweeps(h);
   const double ms =
       std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   for (int r = 0; r < nr; ++r) {

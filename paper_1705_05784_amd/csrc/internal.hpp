@@ -497,6 +497,8 @@ fams_status_t solve_one(Handle* h, const double* q, double* p, const fams_solve_
 // block.hip: nrhs right-hand sides (column-major) in lock-step groups
 fams_status_t solve_block(Handle* h, const double* q, double* p, int nrhs,
                           const fams_solve_opts_t* o, fams_info_t* info);
+// waits with the stream and throws if a sweep gave up (solve.hip)
+void check_sweeps(Handle* h);
 void apply_stage_fp64(Handle* h, const double* r, double* z);
 // the stage's scratch in a caller-provided region: bytes needed, and the
 // stage run with its scratch there (solve.hip)

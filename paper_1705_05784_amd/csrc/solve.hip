@@ -657,19 +657,29 @@ fams_status_t gmres(Handle* h, const Work& k, const double* q, double* p,
   return st;
 }
 
-// a bounded wait that gave up means the sweep's dependency order was broken
-void check_sweeps(Handle* h) {
-  if (!h->sweep_err.get()) return;
-  int e[2] = {};
-  HIPX(hipMemcpyAsync(e, h->sweep_err.get(), sizeof(e), hipMemcpyDeviceToHost, h->stream));
-  HIPX(hipStreamSynchronize(h->stream));
-  h->info.long_waits += e[1];
-  HIPX(hipMemsetAsync(h->sweep_err.get() + 1, 0, sizeof(int), h->stream));
-  if (e[0] != 0) h->tiles.armed = false;
-  FAMS_REQUIRE(e[0] == 0, FAMS_ERR_DEVICE, "ILU(0) sweep: a dependency wait exceeded its bound");
-}
-
 }  // namespace
+
+// A bounded wait that gave up means the sweep's dependency order was broken.
+// The per-medium stage sweeps on a handle of its own, with words of its own.
+// Words that were set are cleared, and the published values of that handle
+// armed again, so that the next call starts anew.
+void check_sweeps(Handle* h) {
+  Handle* gs[2] = {h, h->blk.get()};
+  int e[2][2] = {};
+  for (int k = 0; k < 2; ++k)
+    if (gs[k] && gs[k]->sweep_err.get())
+      HIPX(hipMemcpyAsync(e[k], gs[k]->sweep_err.get(), sizeof(e[k]), hipMemcpyDeviceToHost,
+                          h->stream));
+  HIPX(hipStreamSynchronize(h->stream));
+  for (int k = 0; k < 2; ++k) {
+    if (e[k][0] || e[k][1])
+      HIPX(hipMemsetAsync(gs[k]->sweep_err, 0, sizeof(e[k]), h->stream));
+    if (e[k][0]) gs[k]->tiles.armed = gs[k]->btiles.armed = false;
+    h->info.long_waits += e[k][1];
+  }
+  FAMS_REQUIRE(!e[0][0] && !e[1][0], FAMS_ERR_DEVICE,
+               "ILU(0) sweep: a dependency wait exceeded its bound");
+}
 
 void ensure_workspace(Handle* h, int restart) {
   int m = std::max(restart, 1);
@@ -690,7 +700,8 @@ fams_status_t solve_one(Handle* h, const double* q, double* p, const fams_solve_
                         fams_info_t* info) {
   ensure_workspace(h, o->outer == FAMS_GMRES ? o->restart : 1);
   Work k = work_of(h);
-  if (h->sweep_err.get()) HIPX(hipMemsetAsync(h->sweep_err, 0, sizeof(int), h->stream));
+  for (Handle* g : {h, h->blk.get()})
+    if (g && g->sweep_err.get()) HIPX(hipMemsetAsync(g->sweep_err, 0, sizeof(int), h->stream));
   if (!o->use_initial_guess) HIPX(hipMemsetAsync(p, 0, sizeof(double) * h->n, h->stream));
   auto t0 = std::chrono::steady_clock::now();
   fams_status_t st = o->outer == FAMS_GMRES ? gmres(h, k, q, p, o, info)
