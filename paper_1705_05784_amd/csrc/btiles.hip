@@ -604,8 +604,8 @@ void block_tiles_apply(Handle* h, const T* lu, const T* b, T* x, T* y, const T* 
       LAUNCH(h, "bilu_arm", k_barm<T>, blocks_for(m, kT), kT, 0, m, u ? HU : HL);
     }
     HIPX(hipMemsetAsync(B.ticket, 0, 4 * kTicketStride * sizeof(int), h->stream));
-    B.armed = true;
   }
+  B.armed = false;  // until every launch is queued (see tiles.hip)
   const unsigned long long limit = wait_limit(h);
   auto sweep = [&](int k, bool upper) {
     const TilePhase& p = S.ph[k];
@@ -683,6 +683,7 @@ void block_tiles_apply(Handle* h, const T* lu, const T* b, T* x, T* y, const T* 
              S.ph[0].row1, h->rp.get(), h->ci.get(), lu, x, y);
   }
   sweep(0, true);
+  B.armed = true;
 }
 
 #define FAMS_BLOCK_TILES(K)                                                                     \

@@ -935,11 +935,11 @@ void tile_apply(Handle* h, const T* lu, const T* b, T* x, const T* add, double* 
   T* X = S.st.x.as<T>();
   T* HL = S.st.hl.as<T>();
   T* HU = S.st.hu.as<T>();
-  if (!S.armed) {  // first use, or a sweep that gave up
+  if (!S.armed) {  // first use, or an application that did not come to its end
     LAUNCH(h, "ilu_arm", k_arm<T>, blocks_for(n, kT), kT, 0, (int64_t)n, HL, HU);
     HIPX(hipMemsetAsync(S.ticket, 0, 4 * kTicketStride * sizeof(int), h->stream));
-    S.armed = true;
   }
+  S.armed = false;  // until every launch is queued: the sweeps arm for each other
   if (b) LAUNCH(h, "ilu_gather", k_to_positions<T>, blocks_for(n, kT), kT, 0, n, S.pos.get(), b, X);
   const unsigned long long limit = wait_limit(h);
   const bool two = S.ph.size() == 2;
@@ -1005,6 +1005,7 @@ void tile_apply(Handle* h, const T* lu, const T* b, T* x, const T* add, double* 
              S.ph[0].row1, S.pos.get(), h->rp.get(), h->ci.get(), lu, X);
   }
   sweep(0, true);
+  S.armed = true;
   // back to natural order in a pass of its own: the sweep's rows of a level
   // lie on as many cache lines, and its scattered stores cost more than this
   // pass (upper sweep of the 9.4M-row FP32 system: 567 against 334 us)
