@@ -1327,9 +1327,12 @@ __global__ void k_block_put_rows(double* a, int n, int k0, int nb, const double*
 // each other's negative transposes: the lower triangle holds all of it.
 constexpr int kPt = 32;
 
-// flag <- 1 unless |a_rc - a_cr| <= 1e-8 sqrt(a_rr a_cc) everywhere (rounding
-// of the Galerkin products stays below it; a matrix that is not symmetric, or
-// not positive on the diagonal, exceeds it)
+// flag <- 1 unless |a_rc - a_cr| <= 2^-45 sqrt(a_rr a_cc) everywhere: the
+// rounding of the Galerkin products (at most 1.9e-15 at 0.6M unknowns, 3.0e-15
+// at 2M at contrasts 1e2 and 1e8, 5.4e-15 at 9.4M; the bound is 2.8e-14).  A
+// matrix that is less symmetric than that, or not positive on the diagonal, is
+// inverted as it is.
+constexpr double kSymTol = 0x1p-45;
 __global__ void __launch_bounds__(256) k_sym_check(const double* a, int n, int* flag) {
   __shared__ double T[kPt][kPt + 1];
   if (blockIdx.y > blockIdx.x) return;
@@ -1344,7 +1347,7 @@ __global__ void __launch_bounds__(256) k_sym_check(const double* a, int n, int* 
     if (r >= n || c >= n) continue;
     const double d = a[static_cast<int64_t>(c) * n + r] - T[l][q];
     const double s = sqrt(a[static_cast<int64_t>(r) * n + r] * a[static_cast<int64_t>(c) * n + c]);
-    bad |= !(fabs(d) <= 1e-8 * s);
+    bad |= !(fabs(d) <= kSymTol * s);
   }
   if (bad) *flag = 1;
 }

@@ -18,3 +18,20 @@ def test_block_inverse(n, sym):
     x = fams.dense_op(1, a).cpu().numpy()
     assert np.abs(x @ a - np.eye(n)).max() <= 1e-10
     assert np.array_equal(x, x.T) == sym
+
+
+@pytest.mark.parametrize("off", [1e-6, 1e-9, 1e-12, 1e-13])
+def test_slightly_asymmetric(off):
+    """A matrix that is not quite symmetric is inverted as given, not the one of
+    its lower triangle: x a = I to the same 1e-10."""
+    from paper_1705_05784_amd import fams
+    n = 1801
+    print(f"[dense] asymmetry {off:g}", flush=True)
+    rng = np.random.default_rng(n)
+    m = rng.standard_normal((n, n)) / np.sqrt(n)
+    a = m @ m.T + np.eye(n)
+    d = np.sqrt(np.diag(a))
+    a += np.triu(off * np.outer(d, d) * rng.choice((-1.0, 1.0), (n, n)), 1)
+    x = fams.dense_op(1, a).cpu().numpy()
+    assert np.abs(x @ a - np.eye(n)).max() <= 1e-10
+    assert not np.array_equal(x, x.T)
