@@ -367,8 +367,9 @@ def headline(args, dev):
             "note": "symmetric Gauss-Jordan inverse of A_c, n_c^3 flops over all its launches"}
         gm = st.get("gemm_mfma")
         if gm:
-            # the GEMMs alone: n^2 1024 per block step plus the panel product
-            nb, steps_ = 1024, -(-nc // 1024)
+            # the GEMMs alone: n^2 nb per block step plus the panel product
+            nb = 256 if nc < 2048 else 512
+            steps_ = -(-nc // nb)
             g_flop = sum(1.0 * nc * nc * min(nb, nc - k * nb) + 2.0 * nc * min(nb, nc - k * nb) ** 2
                          for k in range(steps_))
             entries["gemm_mfma"] = {

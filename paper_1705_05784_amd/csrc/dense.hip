@@ -792,7 +792,7 @@ k_gemm_mfma(int m, int p, int k, double alpha, const double* A, int lda, const d
 // staged along their contiguous direction; LDS rows of 128 + 16 doubles put the
 // two rows that a read touches on different banks (staging a column-major B
 // transposed wants 128 + 4).  Slices of 16: two workgroups a CU.  The 36
-// products of an inverse of n = 17810 (5.9 TFLOP): slices of 32 with B column-
+// products of an inverse of n = 17810 in blocks of 1024 (5.9 TFLOP): slices of 32 with B column-
 // major 148 ms, transposed 145 ms, slices of 16 120 ms (53 TFLOP/s in the
 // large ones; a library product of this size reaches 71).
 constexpr int kBT = 128, kBK = 16, kGroupRows = 8;
@@ -1430,9 +1430,18 @@ k_sym_mirror(const double* a, int n, int k0, int nb, double* out, int ld) {
 // with 512, 331 ms with 1024).
 //
 // A symmetric matrix (checked) takes n^3 flops of the 2 n^3: only the lower
-// triangle's tiles of E are formed, and B's new value is C's transposed.  On
-// n = 17810 the products take 120 ms.
+// triangle's tiles of E are formed, and B's new value is C's transposed.  Its
+// errors then come twice where the full form's are independent, and they grow
+// with the explicit inverse of a block: blocks of 512 columns (256 below 2048)
+// keep the inverse as exact as the full form's.  Relative to the full form's
+// with blocks of 1024, the error (Frobenius; condition 1e2, 1e5, 1e8) is 1.00,
+// 1.13 and 1.17 with blocks of 1024, 0.97, 0.28 and 0.04 with 512 at n = 2500;
+// 0.99, 0.91 and 0.52 with 512 at n = 5000; 0.99, 0.02 and below 0.01 with 256
+// at n = 1100 (with 512: 1.04 at condition 1e2).  Time of the inverse of
+// n = 17810: full 321 ms, symmetric 148 ms in blocks of 1024, 151 of 512, 172
+// of 256; of n = 1855: 3.5, 3.3, 3.2 and 3.4 ms.
 constexpr int kOb = 1024;
+constexpr int sym_block(int n) { return n < 2048 ? 256 : 512; }
 
 bool spd_inverse(Handle* h, const double* a, double* inv, int n) {
   DBuf<int> info(&h->alloc, 1);
@@ -1450,8 +1459,9 @@ bool spd_inverse(Handle* h, const double* a, double* inv, int n) {
     HIPX(hipMemcpyAsync(&asym, info.get(), sizeof(int), hipMemcpyDeviceToHost, h->stream));
     HIPX(hipStreamSynchronize(h->stream));
     HIPX(hipMemsetAsync(info, 0, sizeof(int), h->stream));
-    for (int k0 = 0; !asym && k0 < n; k0 += kOb) {
-      const int nb = std::min(kOb, n - k0);
+    const int ob = sym_block(n);
+    for (int k0 = 0; !asym && k0 < n; k0 += ob) {
+      const int nb = std::min(ob, n - k0);
       const unsigned tb = blocks_for(nb, kPt);
       LAUNCH(h, "gje_get", k_sym_mirror, dim3(tb, tb), 256, 0, inv, n, k0, nb, D.get(), nb);
       gje_inner(h, D, nb, info.get());

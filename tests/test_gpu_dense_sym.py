@@ -35,3 +35,22 @@ def test_slightly_asymmetric(off):
     x = fams.dense_op(1, a).cpu().numpy()
     assert np.abs(x @ a - np.eye(n)).max() <= 1e-10
     assert not np.array_equal(x, x.T)
+
+
+@pytest.mark.parametrize("n", [1100, 2500])
+def test_symmetric_form_is_as_exact(n):
+    """The symmetric form's residual is no larger than the full form's, which a
+    matrix 1e-13 away takes (its own residual), at condition 1e6."""
+    from paper_1705_05784_amd import fams
+    print(f"[dense] exactness n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    a = (q * np.logspace(0, -6, n)) @ q.T
+    a = (a + a.T) / 2
+    d = np.sqrt(np.diag(a))
+    b = a + np.triu(1e-13 * np.outer(d, d) * rng.choice((-1.0, 1.0), (n, n)), 1)
+    e = []
+    for m in (a, b):
+        x = fams.dense_op(1, m).cpu().numpy()
+        e.append(np.linalg.norm(x @ m - np.eye(n)))
+    assert e[0] <= e[1], e
