@@ -161,8 +161,11 @@ def measured_traffic(workload, kernel):
 
 
 # a sweep is one launch per phase of its schedule (matrix rows, then fracture
-# rows); the algorithmic bytes are those of a whole sweep, one per prolongation
-SWEEPS = {"ilu_lower": "prolong", "ilu_upper": "prolong",
+# rows); the algorithmic bytes are those of a whole sweep.  Whole sweeps are
+# counted by a kernel that is launched once for each: the last pass of a single
+# one, the prolongation of a lock-step one (single solves prolong once more than
+# they sweep: the next step's coarse half is queued ahead of the stopping test)
+SWEEPS = {"ilu_lower": "ilu_sum", "ilu_upper": "ilu_sum",
           "bilu_lower": "bprolong", "bilu_upper": "bprolong"}
 
 
