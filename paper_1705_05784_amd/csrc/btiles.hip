@@ -381,9 +381,9 @@ k_btile_sweep(BTileArgs<T> a) {
         idx[j] = (x.c[j] < 0 ? kZeroRow : x.c[j]) * KG + rl;
         asm volatile("" : "+v"(idx[j]));
       }
-      const T rinv = kUpper ? T(1) / x.dg : T(0);
-      const bool any_plain =
-          kUpper && __any(x.on && !(__builtin_fabs(static_cast<double>(rinv)) < 1e30));
+      Quotient<T> quot;
+      if constexpr (kUpper) quot.of(x.dg);
+      const bool any_plain = kUpper && __any(x.on && quot.plain());
       const bool any_more = kOver && __any(x.on && (x.row & kMore));
       // published values that were not there at the first read (zero where
       // nothing was read)
@@ -442,14 +442,17 @@ k_btile_sweep(BTileArgs<T> a) {
         }
       if (any_more && x.on && (x.row & kMore))
         btile_overflow<T, N, kUpper>(a, x.row & (kMore - 1), r, s);
-      if constexpr (kUpper)  // s / d (see tiles.hip)
+      if constexpr (kUpper) {
 #pragma unroll
         for (int g = 0; g < N; ++g) {
-          T w = s[g] * rinv;
-          w = fmadd(fmadd(-w, x.dg, s[g]), rinv, w);
-          if (any_plain) w = s[g] / x.dg;
+          T w = quot(s[g], x.dg);
+          if (any_plain) {
+            asm volatile("" : "+v"(s[g]));  // (a branch: not both and a select)
+            w = s[g] / x.dg;
+          }
           s[g] = w;
         }
+      }
       __builtin_memcpy(__builtin_assume_aligned(val + self, N * S), s, N * S);
       asm volatile("" ::: "memory");
       if (lane == 0)

@@ -500,14 +500,16 @@ k_tile_sweep(TileArgs<T> a) {
       for (int g = 0; g < G; ++g) fetch(nx[g], (j + NW) * G + g);
       // LDS indices of the dependencies (rows of other tiles: the zero) and
       // of the row itself (no row: the spare)
-      T rinv[G];
+      Quotient<T> quot[G];
       int idx[G][C], self[G];
       bool plain = false, over = false;
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const bool on = e[g].t >= 0;
-        rinv[g] = kUpper ? T(1) / e[g].dg : T(0);
-        if (kUpper) plain |= on && !(__builtin_fabs(static_cast<double>(rinv[g])) < 1e30);
+        if constexpr (kUpper) {
+          quot[g].of(e[g].dg);
+          plain |= on && quot[g].plain();
+        }
         over |= on && (e[g].meta & kOvf);
 #pragma unroll
         for (int q = 0; q < C; ++q) {
@@ -581,11 +583,11 @@ k_tile_sweep(TileArgs<T> a) {
         if (any_over && e[g].t >= 0 && (e[g].meta & kOvf))
           s = tile_overflow<T, C, kUpper>(a, loc, a.row[e[g].t], tb, te, s);
         if constexpr (kUpper) {
-          // s / d by the correctly rounded reciprocal (off the chain) and one
-          // residual step, which rounds as the division does
-          T qv = s * rinv[g];
-          qv = fmadd(fmadd(-qv, e[g].dg, s), rinv[g], qv);
-          if (any_plain) qv = s / e[g].dg;
+          T qv = quot[g](s, e[g].dg);
+          if (any_plain) {
+            asm volatile("" : "+v"(s));  // (a branch: not both and a select)
+            qv = s / e[g].dg;
+          }
           s = qv;
         }
         loc[self[g]] = s;
