@@ -454,7 +454,12 @@ fams_status_t fams_footprint(int64_t n, int64_t nnz, int64_t n_coarse, int32_t p
   b += 2.0 * 8 * 1024 * nc + 8.0 * 1024 * 1024;                   // block Gauss-Jordan panels
   b += 3.0 * zp * (4 + 8) + 8.0 * (n + 1);                       // A P
   b += 48.0 * 8 * n;                                             // local solutions (setup)
-  b += 2.0 * (4 + 32 + 32 + 4 + 4 + 72 + 8) * n + 24.0 * n;     // sweep schedules, levels
+  // Sweep schedules: at most 260 bytes a row by tiles (codes and factors at eight
+  // places, positions, vectors).  What the lock-step sweeps add (up to 290 bytes a
+  // row, and the published values, up to 16 bytes a row and right-hand side) stays
+  // within the bounds on P and A P: 0.6M rows hold 0.33 to 0.85 of the sum, rows
+  // in random order and the per-medium stage included.
+  b += 336.0 * n;
   b += 240.0 * n;                                                // factorisation records
   b += nnz * 24.0 + n * 400.0;                                   // per-medium stage (smoother 2)
   b += 8.0 * n * (6 + 2 * restart + 1);                          // iteration vectors

@@ -1646,23 +1646,29 @@ fams_status_t solve_block(Handle* h, const double* q, double* p, int nrhs,
   if (!h->alloc.has_hook) {
     // the free device memory, with a margin for the caller
     const size_t held = h->bwk.get() ? block_bytes(h, h->bK, h->bm) : 0;
-    while (K > 2 && block_bytes(h, K, m) > (free_b + held) / 10 * 9) K /= 2;
+    auto tiles = [&](int k) {
+      size_t b = 0;
+      for (Handle* g : {h, h->blk.get()})
+        if (g && h->smoother) b += block_tiles_bytes(g, k);
+      return b;
+    };
+    while (K > 2 && block_bytes(h, K, m) + tiles(K) > (free_b + held) / 10 * 9) K /= 2;
     FAMS_REQUIRE(block_bytes(h, K, m) <= free_b + held, FAMS_ERR_OOM,
                  "no room for the lock-step work space of two right-hand sides");
   } else {
     // an allocation hook may hold memory that the device does not count as
-    // free (a caching allocator): ask the hook for the widest work space and
-    // halve the group while it refuses; a pair last without the tiles
+    // free (a caching allocator): ask the hook for the widest work space
     while (K > 2 && block_bytes(h, K, m) > total_b) K /= 2;
-    for (;;) {
-      try {
-        ensure_block_workspace(h, K, m, plain);
-        break;
-      } catch (const Error& e) {
-        if (e.status != FAMS_ERR_OOM || plain) throw;
-        if (K > 2) K /= 2;
-        else plain = true;
-      }
+  }
+  // halve the group while an allocation is refused; a pair last without the tiles
+  for (;;) {
+    try {
+      ensure_block_workspace(h, K, m, plain);
+      break;
+    } catch (const Error& e) {
+      if (e.status != FAMS_ERR_OOM || plain) throw;
+      if (K > 2) K /= 2;
+      else plain = true;
     }
   }
   const int64_t n = h->n;

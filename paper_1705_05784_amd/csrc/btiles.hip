@@ -512,6 +512,30 @@ size_t rec_bytes(const TilePhase& p) {
 
 }  // namespace
 
+static size_t record_bytes(Handle* h) {  // of one direction
+  size_t b = 0;
+  for (const TilePhase& p : h->tiles.ph)
+    b += (h->precision == FAMS_PREC_MIXED ? rec_bytes<float>(p) : rec_bytes<double>(p)) *
+         (p.row1 - p.row0);
+  return b;
+}
+
+static bool served(Handle* h, int K) {
+  return !h->tiles.ph.empty() && static_cast<double>(h->n) * K * 8 < 4294967296.0 - 512;
+}
+
+// What block_tiles_prepare still has to allocate for groups of K (the published
+// values of another K, which it gives back, not deducted; before the schedule
+// is there, every row may have to be published in both directions).
+size_t block_tiles_bytes(Handle* h, int K) {
+  const BlockTiles& B = h->btiles;
+  if (!served(h, K) || B.K == K) return 0;
+  const size_t n = h->n, s = h->precision == FAMS_PREC_MIXED ? sizeof(float) : sizeof(double);
+  size_t b = B.urec.get() ? 0 : 2 * record_bytes(h);
+  if (!B.built) b += 4 * n * sizeof(int);
+  return b + (B.built ? static_cast<size_t>(B.nlo) + B.nup : 2 * n) * K * s;
+}
+
 // The schedule's part for lock-step sweeps and the published values of
 // groups of K, on first use; false: these sizes are not served.  A refused
 // allocation leaves what is there in use, and the rest to the next call.
@@ -522,7 +546,7 @@ bool block_tiles_prepare(Handle* h, int K) {
   const bool mixed = h->precision == FAMS_PREC_MIXED;
   const size_t s = mixed ? sizeof(float) : sizeof(double);
   const int n = h->n;
-  if (S.ph.empty() || static_cast<double>(n) * K * 8 >= 4294967296.0 - 512) {
+  if (!served(h, K)) {
     B.K = 0;
     return false;
   }
@@ -559,13 +583,10 @@ bool block_tiles_prepare(Handle* h, int K) {
     B = std::move(N);
   }
   if (!B.values) {
-    size_t bytes = 0;
-    for (const TilePhase& p : S.ph)
-      bytes += (mixed ? rec_bytes<float>(p) : rec_bytes<double>(p)) * (p.row1 - p.row0);
     if (!B.urec.get()) {
       Bytes l, u;
-      l.reset(A, bytes);
-      u.reset(A, bytes);
+      l.reset(A, record_bytes(h));
+      u.reset(A, record_bytes(h));
       B.lrec = std::move(l);
       B.urec = std::move(u);
     }

@@ -476,6 +476,7 @@ template <class T>
 void tile_apply(Handle* h, const T* lu, const T* b, T* x, const T* add, double* sum);
 // btiles.hip: the same for K right-hand sides in lock-step
 bool block_tiles_prepare(Handle* h, int K);
+size_t block_tiles_bytes(Handle* h, int K);
 template <class T, int K>
 void block_tiles_apply(Handle* h, const T* lu, const T* b, T* x, T* y, const T* add, double* sum);
 // ilu.hip
