@@ -278,7 +278,7 @@ __global__ void k_gmres_init(GmresState s, int m, const double* beta) {
 
 // One wavefront: h_{j+1,j} = sqrt(sum of npart), then the rotations, from LDS
 // (a serial chain: in global memory each rotation took a round trip).
-constexpr int kGivensLds = 64;  // columns whose rotations fit in LDS
+constexpr int kGivensLds = 64;  // columns of the longest restart (fams_solve: 60)
 __global__ void __launch_bounds__(64)
 k_givens(GmresState s, int m, int j, int nb, const double* npart, double* host) {
   __shared__ double lds[3 * (kGivensLds + 2)];
@@ -286,17 +286,11 @@ k_givens(GmresState s, int m, int j, int nb, const double* npart, double* host) 
   for (int b = threadIdx.x; b < nb; b += 64) sum += npart[b];
   for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
   const double hn = sqrt(sum);
-  const bool in = j < kGivensLds;
-  double* H = s.H + static_cast<int64_t>(j) * (m + 1);
-  double* col = in ? lds : H;
-  const double* cs = in ? lds + kGivensLds + 2 : s.cs;
-  const double* sn = in ? lds + 2 * (kGivensLds + 2) : s.sn;
+  double *col = lds, *cs = lds + kGivensLds + 2, *sn = cs + kGivensLds + 2;
   for (int i = threadIdx.x; i <= j; i += 64) {
     col[i] = s.hcol[i];
-    if (in) {
-      lds[kGivensLds + 2 + i] = s.cs[i];
-      lds[2 * (kGivensLds + 2) + i] = s.sn[i];
-    }
+    cs[i] = s.cs[i];
+    sn[i] = s.sn[i];
   }
   if (threadIdx.x == 0) s.hcol[j + 1] = col[j + 1] = hn;
   __syncthreads();
@@ -321,8 +315,8 @@ k_givens(GmresState s, int m, int j, int nb, const double* npart, double* host) 
     host[1] = hn;
   }
   __syncthreads();
-  if (in)
-    for (int i = threadIdx.x; i <= j + 1; i += 64) H[i] = col[i];
+  double* H = s.H + static_cast<int64_t>(j) * (m + 1);
+  for (int i = threadIdx.x; i <= j + 1; i += 64) H[i] = col[i];
 }
 
 __global__ void k_backsolve(GmresState s, int m, int k) {
@@ -600,6 +594,7 @@ fams_status_t gmres(Handle* h, const Work& k, const double* q, double* p,
                     const fams_solve_opts_t* o, fams_info_t* info) {
   const int64_t n = h->n;
   const int m = std::min(o->restart, k.m);
+  FAMS_REQUIRE(m <= kGivensLds, FAMS_ERR_CAPACITY, "GMRES restart too long");
   double* scratch = k.gs.out;
   resid<double, double, double, double>(h, h->val.get(), p, q, k.r);
   double r0 = norm_host(h, k.r, n, k.part, scratch);
