@@ -196,11 +196,13 @@ typedef struct {
   int64_t peak_device_bytes;  /* most device memory the handle has held at once
                                  (setup, solves and flux reconstructions so far) */
   int64_t long_waits;         /* dependency waits of the dataflow ILU(0) sweeps and
-                                 LU solves that lasted over ~1 ms, all solves so far
-                                 (waits that long mean the workgroups holding the
-                                 dependencies were not running, e.g. another
-                                 process's work on the device; a wait gives up at
-                                 2 s with FAMS_ERR_DEVICE) */
+                                 LU solves that lasted over ~1 ms (over ~8 ms in the
+                                 sweeps by tiles, whose workgroups wait for whole
+                                 tiles), all solves so far (waits that long mean
+                                 the workgroups holding the dependencies were not
+                                 running, e.g. another process's work on the
+                                 device; a wait gives up at 2 s with
+                                 FAMS_ERR_DEVICE) */
   int64_t tiled_rows;         /* rows that the lock-step products with A visit in
                                  slabs of grid lines marched along z (the first
                                  n_matrix rows when they form a 3D grid in natural

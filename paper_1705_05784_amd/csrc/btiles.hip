@@ -282,7 +282,8 @@ __device__ __forceinline__ void btile_overflow(const BTileArgs<T>& a, int i, int
     const T* h = a.H + static_cast<int64_t>(a.slot[a.pos[j]]) * a.K + r;
 #pragma unroll
     for (int v = 0; v < N; ++v)
-      s[v] = fmadd(-a.lu[p], wait_ready<T>(h + v, load_raw<T>(h + v), a.err, a.limit), s[v]);
+      s[v] = fmadd(-a.lu[p],
+                   wait_ready<T, kLongTileWait>(h + v, load_raw<T>(h + v), a.err, a.limit), s[v]);
   }
 }
 
@@ -411,7 +412,7 @@ k_btile_sweep(BTileArgs<T> a) {
             if (lane == 0) atomicOr(a.err, 2);
           }
         } while (__any(missing()));
-        if (!gave_up && lane == 0 && wall_clock64() - t0 > (a.limit >> 11))
+        if (!gave_up && lane == 0 && wall_clock64() - t0 > (a.limit >> kLongTileWait))
           atomicAdd(a.err + 1, 1);
       }
       // the turn: the teams' wavefronts have done slices 0 .. k - 1 (LDS

@@ -409,7 +409,8 @@ __device__ __forceinline__ T tile_overflow(const TileArgs<T>& a, const T* loc, i
     if (k++ < C) continue;
     const int q = a.pos[j];
     const T x = q >= tb && q < te ? loc[q - tb]
-                                  : wait_ready<T>(a.H + q, load_raw<T>(a.H + q), a.err, a.limit);
+                                  : wait_ready<T, kLongTileWait>(a.H + q, load_raw<T>(a.H + q),
+                                                                 a.err, a.limit);
     s = fmadd(-a.lu[p], x, s);
   }
   return s;
@@ -546,7 +547,8 @@ k_tile_sweep(TileArgs<T> a) {
             if (lane == 0) atomicOr(a.err, 2);
           }
         } while (__any(missing()));
-        if (!gave_up && lane == 0 && wall_clock64() - w0 > (a.limit >> 11)) atomicAdd(a.err + 1, 1);
+        if (!gave_up && lane == 0 && wall_clock64() - w0 > (a.limit >> kLongTileWait))
+          atomicAdd(a.err + 1, 1);
       }
       // the turn: groups 0 .. j - 1 done.  LDS accesses of a wavefront are in
       // order, so dependencies read after a turn word of j are final.

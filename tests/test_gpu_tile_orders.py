@@ -107,3 +107,21 @@ def _kernels(g, r):
     k = g.kernel_stats()
     g.profiling(False)
     return k
+
+
+def test_waits_for_a_long_chain_are_not_long_waits(monkeypatch):
+    """Every workgroup in flight waits for all the tiles before it: in a chain in
+    tiles of eight rows for hundreds of hand-overs, over 1 ms, with nothing
+    wrong.  long_waits counts workgroups that are not running (from 8 ms on)."""
+    from paper_1705_05784_amd import fams
+    s = homogeneous(40000, 1, 1, neumann=False)
+    wb, pr, vx, _ = fams.full_grid(s, (100, 1, 1), 4, 1)
+    monkeypatch.setenv("FAMS_ILU_RANGE", "8")
+    g = fams.Solver(s.row_ptr, s.col, s.val, s.n_matrix, wb, pr, vx)
+    Q = torch.from_numpy(np.random.default_rng(5).standard_normal((8, s.n)))
+    for k in (1, 2, 8):
+        g.solve(Q[:k].contiguous() if k > 1 else Q[0], outer="richardson", rtol=0.0, max_iter=2)
+        print(f"[tile orders] {k} right-hand sides, long waits {g.setup_info()['long_waits']}",
+              flush=True)
+    assert g.setup_info()["long_waits"] == 0
+    g.close()
