@@ -52,9 +52,10 @@ namespace {
 // comes by itself: the wavefronts ahead wait for nothing but earlier turns and
 // other tiles, by the clock (2 s, and no longer once an error is flagged).  The
 // count is a guard beyond that, over 4 s at an LDS round trip each.  (Both sweeps
-// of 10k FP64 rows take 112 us so, 114 with the clock in this loop and 115 with
-// the error word too.)
-constexpr int kTurnSpins = 1 << 27;
+// of 10k FP64 rows take 110 us so, 114 with the clock in this loop and 115 with
+// the error word too.  2^27, whose constant is 4 bytes shorter, took 111: the loop
+// is sensitive to where its instructions lie.)
+constexpr int kTurnSpins = 120000000;
 constexpr int kT = 256;
 constexpr int kRunRows = 4096;     // rows of a tile of consecutive rows
 constexpr int kBoxX = 128;         // cells of a box along x
