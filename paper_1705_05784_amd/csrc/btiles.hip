@@ -20,6 +20,7 @@
 // against 2840 us.  The grid rows then move 0.9 to 2.0 GB at 1.0 to 1.4 TB/s;
 // a workgroup with a barrier a slice instead of turns took 1305 for 1077 us.
 #include <algorithm>
+#include <cstdlib>
 #include <type_traits>
 #include <vector>
 
@@ -229,13 +230,23 @@ struct BTileArgs {
 // 2.07M grid rows, K = 16 FP64, with pieces of 32 / 64 / 128 bytes: 1540 / 1077
 // / 1064 us; K = 32 FP32: 1940 / 1478 / 1526 us; of the same systems' fracture
 // rows with pieces of 16 / 32 / 64 bytes: 362 / 301 / 386 us, 551 / 421 / 543 us.
-template <class T, int K, int C>
+// Vectors beyond the last-level cache (256 MB) take pieces twice as wide (kWide):
+// half a line would be read again from memory by another workgroup.  Both sweeps,
+// all phases, with 64 and 32 / 128 and 32 / 128 and 64 bytes: 9.4M rows FP64 K =
+// 16 (1.2 GB a vector) 6096 / 5398 / 5266 us, K = 32 10507 / 9304 / 8909 (level
+// chunks 5181 and 8740); FP32 K = 32 (1.2 GB) 5785 / 5504 / 5479; 2.1M rows FP64
+// K = 32 (0.54 GB) 3166 / 2964 / 3122 (chunks 3053), FP32 K = 32 (0.27 GB) 1990 /
+// 2088 / 2206: from 0.5 GB on for boxes, from 1 GB for runs.
+template <class T, int K, int C, bool kWide>
 struct Lanes {
-  static constexpr int KG = std::min(K, (C > 3 ? 32 : 64) / static_cast<int>(sizeof(T)));
+  static constexpr int KG =
+      std::min(K, (C > 3 ? 32 : 64) * (kWide ? 2 : 1) / static_cast<int>(sizeof(T)));
   static constexpr int N = std::min(K, 16 / static_cast<int>(sizeof(T)));  // values a lane
   static constexpr int per_row = KG / N;
   static constexpr int rows = 64 / per_row;  // of one access
 };
+template <class T, int K>
+constexpr bool kCanWiden = K * sizeof(T) >= 128;
 constexpr int kWaves = 16;
 
 // N values at a byte offset of a buffer (past the end: zero, dropped)
@@ -288,11 +299,11 @@ __device__ __forceinline__ void btile_overflow(const BTileArgs<T>& a, int i, int
 }
 
 // A workgroup takes tiles by ticket in dependency order.
-template <class T, int K, int C, bool kUpper, bool kOver>
+template <class T, int K, int C, bool kUpper, bool kOver, bool kWide>
 __global__ void __launch_bounds__(64 * kWaves)
 k_btile_sweep(BTileArgs<T> a) {
   using U = typename Sentinel<T>::U;
-  using L = Lanes<T, K, C>;
+  using L = Lanes<T, K, C, kWide>;
   constexpr int W = C <= 4 ? 4 : 8, S = sizeof(T), N = L::N, KG = L::KG, kGroups = K / KG;
   constexpr int kTeam = 64 / L::rows, kTeams = kWaves / kTeam;
   using R = Rec<T, W>;
@@ -521,8 +532,39 @@ static size_t record_bytes(Handle* h) {  // of one direction
   return b;
 }
 
+// Whether the tiles are the faster form for groups of K.  With boxes of a grid
+// they are.  Where every row is in a run of consecutive rows, tiles have many
+// narrow levels: a task (a tile and 32 bytes of each row's values) holds a
+// workgroup for some time a slice, and the device runs some 256 at a time, so
+// that a sweep takes time by the number of tasks; the level chunks take theirs by
+// the levels and rows, whatever the width.  Both sweeps, tiles / chunks in us, of
+// grids with one coupling out of place:
+//   0.62M rows  FP64 K = 8 1048 / 1666, 16 1478 / 1543, 32 2225 / 1566
+//   2.29M rows  FP64 K = 4 1861 / 3168, 8 2990 / 2922, 16 5471 / 2795, 32 9449 / 3053
+//               FP32 K = 16 1852 / 2856, 32 3342 / 2853
+//   9.4M rows   FP64 K = 2 4605 / 7753, 4 6182 / 5828, 8 11994 / 5122, 32 42405 / 8745
+//               FP32 K = 8 3229 / 5164, 16 6614 / 4667, 32 13513 / 5863
+// and of 2.29M rows in random order (82 slices a tile instead of 239) FP64 K = 8
+// 1882 / 2033, 16 3138 / 2113, FP32 K = 16 1367 / 1882, 32 2307 / 2185.  Few wide
+// levels (random order: 46 rows a slice instead of 17 to 31) leave the chunks the
+// better form of wide rows at any size: 0.12M rows FP64 K = 16 872 / 714.
+static bool tiles_faster(Handle* h, int K) {
+  const TileSched& S = h->tiles;
+  if (S.ph[0].boxes) return true;
+  const bool mixed = h->precision == FAMS_PREC_MIXED;
+  const int ntiles = S.ph[0].ntiles, row = K * (mixed ? 4 : 8);
+  const double per_tile = static_cast<double>(S.slices) / ntiles;
+  if (row >= 128 && h->n >= 40.0 * S.slices) return false;
+  const double task = (mixed ? 0.8 + 0.003 * per_tile : 1.0 + 0.0065 * per_tile) *
+                      (row < 32 ? 0.75 : 1.0);
+  const double levels = static_cast<double>(h->info.ilu_levels_lower + h->info.ilu_levels_upper);
+  const double chunks = (2.5 * levels + 0.2e-3 * h->n) * (K == 2 ? 1.5 : K == 4 ? 1.05 : 1.0);
+  return ntiles * std::max(1, row / 32) * task <= chunks;
+}
+
 static bool served(Handle* h, int K) {
-  return !h->tiles.ph.empty() && static_cast<double>(h->n) * K * 8 < 4294967296.0 - 512;
+  return !h->tiles.ph.empty() && static_cast<double>(h->n) * K * 8 < 4294967296.0 - 512 &&
+         tiles_faster(h, K);
 }
 
 // What block_tiles_prepare still has to allocate for groups of K (the published
@@ -580,6 +622,7 @@ bool block_tiles_prepare(Handle* h, int K) {
     HIPX(hipStreamSynchronize(h->stream));
     N.nlo = cnt[0];
     N.nup = cnt[1];
+    if (const char* e = std::getenv("FAMS_SWEEP_WIDE")) N.wide_from = std::atof(e);
     N.built = true;
     B = std::move(N);
   }
@@ -667,21 +710,29 @@ void block_tiles_apply(Handle* h, const T* lu, const T* b, T* x, T* y, const T* 
     a.ticket_clear = B.ticket.get() + (upper ? 0 : 2) * kTicketStride;
     a.err = h->sweep_err.get();
     a.limit = limit;
-    const int KG = p.C > 3 ? Lanes<T, K, 4>::KG : Lanes<T, K, 3>::KG;
+    const double bytes = static_cast<double>(n) * K * sizeof(T);
+    const bool wide = kCanWiden<T, K> && bytes >= (B.wide_from >= 0 ? B.wide_from
+                                                   : p.C > 3 ? 1e9 : 0.5e9);
+    const int KG = std::min(K, (p.C > 3 ? 32 : 64) * (wide ? 2 : 1) / static_cast<int>(sizeof(T)));
     const size_t lds = static_cast<size_t>(kZeroRow + 1) * KG * sizeof(T) +
                        (p.max_slices + 1) * sizeof(int);
     FAMS_REQUIRE(lds <= static_cast<size_t>(lds_hw_budget(h)), FAMS_ERR_CAPACITY,
                  "ILU tile does not fit in LDS");
-#define FAMS_BTILE(C, UP, OVER)                                                        \
-  do {                                                                                 \
-    allow_lds(reinterpret_cast<const void*>(&k_btile_sweep<T, K, C, UP, OVER>), lds);  \
-    LAUNCH(h, UP ? "bilu_upper" : "bilu_lower", (k_btile_sweep<T, K, C, UP, OVER>),    \
-           std::min(p.ntiles * (K / KG), 2048), 64 * kWaves, lds, a);                             \
+#define FAMS_BTILE(C, UP, OVER, WIDE)                                                       \
+  do {                                                                                      \
+    allow_lds(reinterpret_cast<const void*>(&k_btile_sweep<T, K, C, UP, OVER, WIDE>), lds); \
+    LAUNCH(h, UP ? "bilu_upper" : "bilu_lower", (k_btile_sweep<T, K, C, UP, OVER, WIDE>),   \
+           std::min(p.ntiles * (K / KG), 2048), 64 * kWaves, lds, a);                       \
   } while (0)
-#define FAMS_BTILES(C, OVER)              \
-  do {                                    \
-    if (upper) FAMS_BTILE(C, true, OVER); \
-    else FAMS_BTILE(C, false, OVER);      \
+#define FAMS_BTILE_W(C, UP, OVER)                                        \
+  do {                                                                   \
+    if (wide) FAMS_BTILE(C, UP, OVER, (kCanWiden<T, K>));                \
+    else FAMS_BTILE(C, UP, OVER, false);                                 \
+  } while (0)
+#define FAMS_BTILES(C, OVER)                \
+  do {                                      \
+    if (upper) FAMS_BTILE_W(C, true, OVER); \
+    else FAMS_BTILE_W(C, false, OVER);      \
   } while (0)
     switch (p.C) {
       case 3: FAMS_BTILES(3, false); break;
@@ -692,6 +743,7 @@ void block_tiles_apply(Handle* h, const T* lu, const T* b, T* x, T* y, const T* 
         break;
     }
 #undef FAMS_BTILES
+#undef FAMS_BTILE_W
 #undef FAMS_BTILE
   };
   sweep(0, false);

@@ -253,6 +253,7 @@ struct TileSched {
   std::vector<TilePhase> ph;  // empty: no schedule
   DBuf<int> pos, row, meta;   // row -> position, its inverse, flags per position
   DBuf<int> tslice, slice;    // tile -> slices, slice -> first position
+  int slices = 0;
   DBuf<int> lcol, ucol;
   DBuf<int> pre;              // first-phase rows coupled to the second
   int npre = 0;
@@ -276,6 +277,7 @@ struct BlockTiles {
   int nlo = 0, nup = 0, K = 0;
   Bytes lrec, urec, hl, hu;
   bool built = false, values = false, armed = false;
+  double wide_from = -1;  // FAMS_SWEEP_WIDE: bytes of a vector from which pieces are wide
 };
 
 // Host phase timer: with FAMS_SETUP_TIMING set, mark() synchronises the

@@ -850,6 +850,7 @@ void build_tiles(Handle* h, int cap) {
     HIPX(hipMemsetAsync(small, 0, 8 * sizeof(int), h->stream));
     order();
   }
+  S.slices = total;
   S.slice.reset(A, total + 1);
   HIPX(hipMemcpyAsync(S.slice.get() + total, tstart.get() + nt, sizeof(int),
                       hipMemcpyDeviceToDevice, h->stream));
