@@ -165,8 +165,7 @@ LAUNCH_NAMES = {
 for _c in (3, 4, 8):
     for _up, _name in (("false", "lower"), ("true", "upper")):
         LAUNCH_NAMES[f"k_tile_sweep<float, {_c}, {_up}>"] = f"ilu_{_name}"
-        for _over in ("false", "true"):
-            LAUNCH_NAMES[f"k_btile_sweep<float, 32, {_c}, {_up}, {_over}>"] = f"bilu_{_name}"
+        LAUNCH_NAMES[f"k_btile_sweep<float, 32, {_c}, {_up},*"] = f"bilu_{_name}"
 
 
 def _main(argv):
