@@ -395,7 +395,11 @@ k_btile_sweep(BTileArgs<T> a) {
       }
       Quotient<T> quot;
       if constexpr (kUpper) quot.of(x.dg);
-      const bool any_plain = kUpper && __any(x.on && quot.plain());
+      bool plain = false;
+      if constexpr (kUpper)
+#pragma unroll
+        for (int g = 0; g < N; ++g) plain |= x.on && quot.plain(e.in[g]);
+      const bool any_plain = kUpper && __any(plain);
       const bool any_more = kOver && __any(x.on && (x.row & kMore));
       // published values that were not there at the first read (zero where
       // nothing was read)

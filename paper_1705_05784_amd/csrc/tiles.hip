@@ -510,7 +510,7 @@ k_tile_sweep(TileArgs<T> a) {
         const bool on = e[g].t >= 0;
         if constexpr (kUpper) {
           quot[g].of(e[g].dg);
-          plain |= on && quot[g].plain();
+          plain |= on && quot[g].plain(e[g].in);
         }
         over |= on && (e[g].meta & kOvf);
 #pragma unroll

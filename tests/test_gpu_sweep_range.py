@@ -1,7 +1,7 @@
 """The tiled sweeps' divisions by the diagonal at the ends of the numbers' range:
-quotients that overflow, small inputs (below the smallest normal number in FP32;
-in FP64 down to where the residual of a quotient is exact), diagonals whose
-reciprocal lies below the smallest normal number.  The oracle is the level-by-level form
+quotients that overflow, small inputs (down to where the residual of an FP64
+quotient is exact, and around the smallest normal number of either precision),
+diagonals whose reciprocal lies below the smallest normal number.  The oracle is the level-by-level form
 (FAMS_ILU_RANGE=0), which divides: the same bits, infinities included; in
 lock-step the single step's infinities."""
 import dataclasses
@@ -36,7 +36,7 @@ def _with(s, A):
 
 
 @pytest.mark.parametrize("precision", [0, 1])
-@pytest.mark.parametrize("kind", ["overflow", "tiny", "large diagonal"])
+@pytest.mark.parametrize("kind", ["overflow", "tiny", "tiniest", "large diagonal"])
 def test_division_at_the_ends(kind, precision, monkeypatch):
     from paper_1705_05784_amd import fams
     s, spec = small_case("3d")
@@ -49,6 +49,8 @@ def test_division_at_the_ends(kind, precision, monkeypatch):
         r[c] = 4.0 * s.csr()[c, c] * MAX[precision]
     elif kind == "tiny":
         r *= 2.0 ** (-135 if precision else -900)
+    elif kind == "tiniest":
+        r *= 2.0 ** (-145 if precision else -1020)
     else:   # diagonals up to the largest power of two; small inputs, so that nothing overflows
         e = (126 if precision else 1022) - int(np.ceil(np.log2(s.csr().diagonal().max())))
         s = _with(s, s.csr() * 2.0 ** e)
